@@ -14,237 +14,23 @@
 // In the chiral basis G_k = [[0, m_k], [m_k, 0]] with m_k = -i sigma_k, one
 // entry per row and column.
 //
-// Each site (coarse site and block slice) writes its weighted density; a
-// second pass adds the densities of every time slice in a fixed order, so the
-// result does not depend on launch or batch composition.
+// Each workgroup writes one partial sum per time slice; a second pass adds the
+// partials of every time slice in a fixed order, so the result does not depend
+// on launch or batch composition.
 #include "mglma_internal.h"
 
 #include <mutex>
 
-struct Term {
-    int a, b, k;      // field of set i, field of set j, gamma index
-    double cre, cim;  // weight
-};
-#define MAXTERMS 36
-struct TermList {
-    Term t[MAXTERMS];
-    int n;
-};
-
-// point-source terms: for each k and source spin s_a and colour c:
-// b = (s_b, c) with s_b the column of row s_a of gamma_k gamma5 = -G_k
-static TermList point_terms() {
-    TermList L;
-    L.n = 0;
-    for (int k = 1; k <= 3; ++k)
-        for (int sa = 0; sa < 4; ++sa) {
-            int sb;
-            double cr, ci;
-            gk_row(k, sa, &sb, &cr, &ci);
-            for (int col = 0; col < 3; ++col) {
-                Term& T = L.t[L.n++];
-                T.a = 3 * sa + col;
-                T.b = 3 * sb + col;
-                T.k = k;
-                // -1/3 * (gamma_k gamma5)_{sa sb} = -1/3 * (-G_k[sa][sb])
-                T.cre = cr / 3.0;
-                T.cim = ci / 3.0;
-            }
-        }
-    return L;
-}
-
-// stochastic terms: for each k and source spin s: s' = row of the entry in column s
-static TermList stoch_terms(double L3) {
-    TermList L;
-    L.n = 0;
-    for (int k = 1; k <= 3; ++k)
-        for (int sp = 0; sp < 4; ++sp) {
-            int s;
-            double cr, ci;
-            gk_row(k, sp, &s, &cr, &ci);   // G_k[sp][s] = (cr, ci)
-            Term& T = L.t[L.n++];
-            T.a = s;
-            T.b = sp;
-            T.k = k;
-            // -1/(3 L^3) conj(G_k[s'][s])
-            T.cre = -cr / (3.0 * L3);
-            T.cim = ci / (3.0 * L3);
-        }
-    return L;
-}
-
-// density[i] = sum_terms w * psi^j_b(x)^+ G_k psi^i_a(x)
-__global__ __launch_bounds__(256) void k_fine_density(Geo g, const double2* __restrict__ pi,
-                                                      const double2* __restrict__ pj, TermList T,
-                                                      double2* __restrict__ dens) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= g.V) return;
-    const size_t V = g.V;
-    cx<double> tot = cmk(0.0, 0.0);
-    for (int q = 0; q < T.n; ++q) {
-        const Term tm = T.t[q];
-        const double2* A = pi + (size_t)tm.a * 12 * V + i;
-        const double2* B = pj + (size_t)tm.b * 12 * V + i;
-        cx<double> s = cmk(0.0, 0.0);
-        for (int sp = 0; sp < 4; ++sp) {
-            int tc;
-            double cr, ci;
-            gk_row(tm.k, sp, &tc, &cr, &ci);
-            cx<double> acc = cmk(0.0, 0.0);
-            for (int col = 0; col < 3; ++col)
-                cjmac(acc, ldc<double2, double>(B + (size_t)(3 * sp + col) * V),
-                      ldc<double2, double>(A + (size_t)(3 * tc + col) * V));
-            s = s + cmk(cr, ci) * acc;
-        }
-        tot = tot + cmk(tm.cre, tm.cim) * s;
-    }
-    dens[i] = make_double2(tot.re, tot.im);
-}
-
-// out[x0] = sum over the spatial sites of slice x0 (lexicographic order)
-__global__ __launch_bounds__(256) void k_slice_sum(Geo g, const double2* __restrict__ dens, double2* __restrict__ out) {
-    const int x0 = blockIdx.x;
-    __shared__ double lre[256], lim[256];
-    double re = 0.0, im = 0.0;
-    for (int xs = threadIdx.x; xs < g.V3; xs += blockDim.x) {
-        int x[4];
-        int r = xs;
-        x[3] = r % g.L[3]; r /= g.L[3];
-        x[2] = r % g.L[2]; r /= g.L[2];
-        x[1] = r;
-        x[0] = x0;
-        double2 v = dens[geo_index(g, x)];
-        re += v.x;
-        im += v.y;
-    }
-    lre[threadIdx.x] = re;
-    lim[threadIdx.x] = im;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (threadIdx.x < o) {
-            lre[threadIdx.x] += lre[threadIdx.x + o];
-            lim[threadIdx.x] += lim[threadIdx.x + o];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[x0] = make_double2(lre[0], lim[0]);
-}
-
-// coarse density per (coarse site y, block slice t): sum_terms w * u^+ Gamma1_k(y,t) v,
-// u = c^j_b(y), v = c^i_a(y), Gamma1 = [[0, Gb], [-Gb^+, 0]]:
-//   u^+ Gamma v = u0^+ Gb v1 - conj(v0^+ Gb u1)
-__global__ __launch_bounds__(256) void k_coarse_density(Geo g, int Nv, const double2* __restrict__ G1,
-                                                        const double2* __restrict__ ci,
-                                                        const double2* __restrict__ cj, TermList T,
-                                                        double2* __restrict__ dens) {
-    const int y = blockIdx.x / g.b[0], t = blockIdx.x % g.b[0];
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int nc = 2 * Nv;
-    const size_t V1 = g.V1;
-    __shared__ double wre[4], wim[4];
-    cx<double> wt = cmk(0.0, 0.0);   // this wave's weighted sum (lane 0)
-    for (int q = w; q < T.n; q += 4) {
-        const Term tm = T.t[q];
-        const double2* Gb = G1 + (((size_t)y * g.b[0] + t) * 3 + (tm.k - 1)) * Nv * Nv;
-        const double2* u = cj + ((size_t)tm.b * V1 + y) * nc;
-        const double2* v = ci + ((size_t)tm.a * V1 + y) * nc;
-        cx<double> s1 = cmk(0.0, 0.0), s2 = cmk(0.0, 0.0);
-        for (int cd = lane; cd < Nv * Nv; cd += 64) {
-            int c = cd / Nv, d = cd % Nv;
-            cx<double> gcd = ldc<double2, double>(Gb + cd);
-            cx<double> t1 = gcd * ldc<double2, double>(v + Nv + d);
-            cjmac(s1, ldc<double2, double>(u + c), t1);
-            cx<double> t2 = gcd * ldc<double2, double>(u + Nv + d);
-            cjmac(s2, ldc<double2, double>(v + c), t2);
-        }
-        for (int o = 32; o > 0; o >>= 1) {
-            s1.re += __shfl_xor(s1.re, o, 64); s1.im += __shfl_xor(s1.im, o, 64);
-            s2.re += __shfl_xor(s2.re, o, 64); s2.im += __shfl_xor(s2.im, o, 64);
-        }
-        cx<double> val = s1 - conj(s2);
-        wt = wt + cmk(tm.cre, tm.cim) * val;
-    }
-    if (lane == 0) { wre[w] = wt.re; wim[w] = wt.im; }
-    __syncthreads();
-    if (threadIdx.x == 0)
-        dens[blockIdx.x] = make_double2(wre[0] + wre[1] + wre[2] + wre[3], wim[0] + wim[1] + wim[2] + wim[3]);
-}
-
-// out[x0] = sum over the coarse sites of time row x0 / b0 of dens[y][x0 % b0]
-__global__ void k_coarse_slice_sum(Geo g, const double2* __restrict__ dens, double2* __restrict__ out) {
-    const int x0 = blockIdx.x * blockDim.x + threadIdx.x;
-    if (x0 >= g.L[0]) return;
-    const int b0 = g.b[0], y0 = x0 / b0, t = x0 % b0, rowsz = g.V1 / g.L1[0];
-    double re = 0.0, im = 0.0;
-    for (int ys = 0; ys < rowsz; ++ys) {
-        double2 v = dens[(size_t)(y0 * rowsz + ys) * b0 + t];
-        re += v.x;
-        im += v.y;
-    }
-    out[x0] = make_double2(re, im);
-}
-
-static int finish_host(mglma_ctx* c, const double2* out_dev, int t0, double* C_host) {
-    const int L0 = c->L[0];
-    double* h;
-    MG_TRY(mg_host(c, 2 * (size_t)L0, &h));
-    HIP_TRY(hipMemcpyAsync(h, out_dev, (size_t)L0 * 16, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    for (int t = 0; t < L0; ++t) {
-        int x0 = (t0 + t) % L0;
-        C_host[2 * t] = h[2 * x0];
-        C_host[2 * t + 1] = h[2 * x0 + 1];
-    }
-    return MGLMA_OK;
-}
-
-static int fine_contract(mglma_ctx* c, const double* pi, const double* pj, const TermList& T, int t0, double* C) {
-    const Geo& g = c->geo;
-    double2 *dens, *out;
-    MG_TRY(mg_scratch(c, 28, (size_t)g.V * 16, (void**)&dens));
-    MG_TRY(mg_scratch(c, 29, (size_t)g.L[0] * 16 + 256, (void**)&out));
-    hipLaunchKernelGGL(k_fine_density, dim3((g.V + 255) / 256), dim3(256), 0, c->stream, g, (const double2*)pi,
-                       (const double2*)pj, T, dens);
-    HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_slice_sum, dim3(g.L[0]), dim3(256), 0, c->stream, g, dens, out);
-    HIP_TRY(hipGetLastError());
-    return finish_host(c, out, t0, C);
-}
-
-static int coarse_contract(mglma_ctx* c, const double* ci, const double* cj, const TermList& T, int t0, double* C) {
-    const Geo& g = c->geo;
-    double2 *dens, *out;
-    MG_TRY(mg_scratch(c, 28, (size_t)g.V1 * g.b[0] * 16, (void**)&dens));
-    MG_TRY(mg_scratch(c, 29, (size_t)g.L[0] * 16 + 256, (void**)&out));
-    hipLaunchKernelGGL(k_coarse_density, dim3(g.V1 * g.b[0]), dim3(256), 0, c->stream, g, c->Nv, c->G1,
-                       (const double2*)ci, (const double2*)cj, T, dens);
-    HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_coarse_slice_sum, dim3((g.L[0] + 63) / 64), dim3(64), 0, c->stream, g, dens, out);
-    HIP_TRY(hipGetLastError());
-    return finish_host(c, out, t0, C);
-}
-
-extern "C" int mglma_contract_point(mglma_ctx* c, const double* pi, const double* pj, int y0, double* C) {
-    if (!c || !pi || !pj || !C || y0 < 0 || y0 >= (c ? c->L[0] : 0)) return MGLMA_ERR_ARG;
-    return fine_contract(c, pi, pj, point_terms(), y0, C);
-}
-
-extern "C" int mglma_contract_point_coarse(mglma_ctx* c, const double* ci, const double* cj, int y0, double* C) {
-    if (!c || !ci || !cj || !C || y0 < 0 || y0 >= (c ? c->L[0] : 0)) return MGLMA_ERR_ARG;
-    if (!c->have_subspace) return MGLMA_ERR_NO_SUBSPACE;
-    return coarse_contract(c, ci, cj, point_terms(), y0, C);
-}
-
-extern "C" int mglma_contract_stoch(mglma_ctx* c, const double* pi, const double* pj, int tn, double* C) {
-    if (!c || !pi || !pj || !C || tn < 0 || tn >= (c ? c->L[0] : 0)) return MGLMA_ERR_ARG;
-    return fine_contract(c, pi, pj, stoch_terms((double)c->geo.V3), tn, C);
-}
-
-extern "C" int mglma_contract_stoch_coarse(mglma_ctx* c, const double* ci, const double* cj, int tn, double* C) {
-    if (!c || !ci || !cj || !C || tn < 0 || tn >= (c ? c->L[0] : 0)) return MGLMA_ERR_ARG;
-    if (!c->have_subspace) return MGLMA_ERR_NO_SUBSPACE;
-    return coarse_contract(c, ci, cj, stoch_terms((double)c->geo.V3), tn, C);
+// Both kinds have the same form: with columns (source spin sa, source colour c;
+// c = 0 alone for the wall source) and sb the column of row sa of G_k,
+//   scale * sum_k sum_{sa, c} G_k[sa][sb] psi^j_{(sb,c)}(x)^+ G_k psi^i_{(sa,c)}(x),
+// scale = 1/3 (point: (gamma_k gamma5)_{ab} = -G_k[a][b]) or 1/(3 L^3) (wall:
+// G_k is anti-Hermitian, -conj(G_k[s'][s]) = G_k[s][s']).
+// G_k[s][t] is non-zero at t = gk_col(k, s) only; the products of two entries
+// of one G_k are real: G_k[s][.] G_k[s'][.] = gk_sign(k, s, s').
+__device__ constexpr int gk_col(int k, int s) { return k < 3 ? 3 - s : s ^ 2; }
+__device__ constexpr double gk_sign(int k, int s, int t) {
+    return k == 1 ? -1.0 : ((k == 2) == ((s ^ t) & 1) ? -1.0 : 1.0);
 }
 
 // ---------------------------------------------------------------------------
@@ -272,14 +58,15 @@ struct SrcTimes {
     int t[LV_MAXSRC];
 };
 
-// chunks per time slice: about 1024 fine sites or 16 coarse sites per chunk
+// chunks per time slice (at most LV_MAXCHUNK): whole passes of 256 threads over
+// the fine sites of a slice, single coarse sites where there are that few
 static int fine_chunks(const Geo& g) {
-    int n = g.V3 / 1024;
-    return n < 1 ? 1 : (n > LV_MAXCHUNK ? LV_MAXCHUNK : n);
+    const int n = (g.V3 + 255) / 256, per = (n + LV_MAXCHUNK - 1) / LV_MAXCHUNK;
+    return (n + per - 1) / per;
 }
 static int coarse_chunks(const Geo& g) {
-    int n = (g.V1 / g.L1[0]) / 16;
-    return n < 1 ? 1 : (n > LV_MAXCHUNK ? LV_MAXCHUNK : n);
+    const int n = g.V1 / g.L1[0];
+    return n > LV_MAXCHUNK ? LV_MAXCHUNK : n;
 }
 
 // workgroup sum of one complex per thread (256 threads), fixed order
@@ -299,10 +86,21 @@ __device__ __forceinline__ double2 wg_sum256(double re, double im) {
 }
 
 // grid (L0 * nchunk, nsrc, npair), block 256; fields of source n start at
-// column n * ncol of each piece; part index ((pair0 + p) * nsrc + n) * L0 + x0,
-// times LV_MAXCHUNK, plus the chunk
-__global__ __launch_bounds__(256) void k_fine_slice_part(Geo g, int nchunk, int ncol, int nsrc, int pair0, PairSet P,
-                                                         TermList T, double2* __restrict__ part) {
+// column n * 4 NCS of each piece (column sa * NCS + c, NCS source colours);
+// part index ((pair0 + p) * nsrc + n) * L0 + x0, times LV_MAXCHUNK, plus the
+// chunk.  SAME: psi_i = psi_j (the level rows), each field read once.
+//
+// Bound: HBM, the 4 NCS fields of a source read once (1.53 GB for the 12
+// columns on 48 x 24^3).  For one source colour c and one sink colour the sum
+// only couples the 4 x 4 matrix of (source spin, sink spin) entries, so a
+// thread loads those 16 values of its site in one run of independent
+// coalesced loads and forms all 3 x 4 x 4 products from registers.  (Walking
+// the 36 (k, sa, c) terms and loading both fields of each re-read every value
+// six times through the caches: 1.34 ms; this form 0.26 ms,
+// 5.8 TB/s.)
+template <int NCS, bool SAME>
+__global__ __launch_bounds__(256) void k_fine_slice_part(Geo g, int nchunk, int nsrc, int pair0, PairSet P,
+                                                         double scale, double2* __restrict__ part) {
     const int x0 = blockIdx.x / nchunk, ch = blockIdx.x - x0 * nchunk;
     const int n = blockIdx.y, p = blockIdx.z;
     const int b0 = g.b[0], y0 = x0 / b0, l0 = x0 - y0 * b0;
@@ -310,77 +108,182 @@ __global__ __launch_bounds__(256) void k_fine_slice_part(Geo g, int nchunk, int 
     const long tot = (long)rowsz * b123;
     const int e0 = (int)(tot * ch / nchunk), e1 = (int)(tot * (ch + 1) / nchunk);
     const size_t V = g.V;
-    const double2* pi = P.pi[p] + (size_t)n * ncol * 12 * V;
-    const double2* pj = P.pj[p] + (size_t)n * ncol * 12 * V;
+    const double2* pi = P.pi[p] + (size_t)n * 4 * NCS * 12 * V;
+    const double2* pj = P.pj[p] + (size_t)n * 4 * NCS * 12 * V;
     double re = 0.0, im = 0.0;
     for (int e = e0 + (int)threadIdx.x; e < e1; e += 256) {
         const int kb = e / b123, lo = e - kb * b123;
         const int i = (y0 * rowsz + kb) * g.Vb + l0 * b123 + lo;
-        cx<double> tot_s = cmk(0.0, 0.0);
-        for (int q = 0; q < T.n; ++q) {
-            const Term tm = T.t[q];
-            const double2* A = pi + (size_t)tm.a * 12 * V + i;
-            const double2* B = pj + (size_t)tm.b * 12 * V + i;
-            cx<double> s = cmk(0.0, 0.0);
-            for (int sp = 0; sp < 4; ++sp) {
-                int tc;
-                double cr, ci;
-                gk_row(tm.k, sp, &tc, &cr, &ci);
-                cx<double> acc = cmk(0.0, 0.0);
-                for (int col = 0; col < 3; ++col)
-                    cjmac(acc, ldc<double2, double>(B + (size_t)(3 * sp + col) * V),
-                          ldc<double2, double>(A + (size_t)(3 * tc + col) * V));
-                s = s + cmk(cr, ci) * acc;
+#pragma unroll 1
+        for (int q = 0; q < 3 * NCS; ++q) {
+            const int c = q / 3, col = q - 3 * c;
+            const size_t off = ((size_t)c * 12 + col) * V + i;
+            double2 A[4][4], B[4][4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int sp = 0; sp < 4; ++sp) A[s][sp] = pi[off + (size_t)(s * NCS * 12 + 3 * sp) * V];
+            if (!SAME) {
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+#pragma unroll
+                    for (int sp = 0; sp < 4; ++sp) B[s][sp] = pj[off + (size_t)(s * NCS * 12 + 3 * sp) * V];
             }
-            tot_s = tot_s + cmk(tm.cre, tm.cim) * s;
+#pragma unroll
+            for (int k = 1; k <= 3; ++k)
+#pragma unroll
+                for (int sa = 0; sa < 4; ++sa)
+#pragma unroll
+                    for (int sp = 0; sp < 4; ++sp) {
+                        const double2 b = SAME ? A[gk_col(k, sa)][sp] : B[gk_col(k, sa)][sp];
+                        const double2 a = A[sa][gk_col(k, sp)];
+                        const double sg = gk_sign(k, sa, sp);
+                        re = fma(sg * b.x, a.x, re);
+                        re = fma(sg * b.y, a.y, re);
+                        if (!SAME) {
+                            im = fma(sg * b.x, a.y, im);
+                            im = fma(-sg * b.y, a.x, im);
+                        }
+                    }
         }
-        re += tot_s.re;
-        im += tot_s.im;
     }
-    const double2 v = wg_sum256(re, im);
+    // (SAME: the sum is real; the product carries NaN and infinity into both parts)
+    const double2 v = wg_sum256(scale * re, SAME ? 0.0 * re : scale * im);
     if (threadIdx.x == 0)
         part[((((size_t)(pair0 + p) * nsrc + n) * g.L[0] + x0) * LV_MAXCHUNK) + ch] = v;
 }
 
-// grid (L0 * nchunk, nsrc, npair), block 256 (4 wavefronts over the coarse
-// sites of the chunk, lanes over the Nv x Nv entries of (gamma5 gamma_k)_1)
-__global__ __launch_bounds__(256) void k_coarse_slice_part(Geo g, int Nv, int nchunk, int ncol, int nsrc, int pair0,
-                                                           const double2* __restrict__ G1, PairSet P, TermList T,
+// Coarse pieces on the FP64 matrix cores (v_mfma_f64_16x16x4): with Gb the
+// stored alpha = 0 x alpha = 1 block of (gamma5 gamma_k)_1(y, t),
+//   u^+ Gamma v = u_0^+ Gb v_1 - conj(v_0^+ Gb u_1),
+// and T = Gb [v_1 of 16 columns] is a GEMM whose columns are 16 / (4 NCS)
+// (piece, source) groups.  One workgroup per (block row y0, chunk of its
+// coarse sites, column tile), the tiles of a chunk back to back on one XCD;
+// wavefront w takes the block time slice w % b0 (every ns-th site of the
+// chunk when b0 <= 2), so Gb is read once per tile in 64-byte runs and each
+// lane then weights its own rows of T with conj(u_0).  MFMA lane (lr, lq)
+// supplies A[row lr][4 s + lq], B[4 s + lq][col lr]; Nv is walked in steps of
+// four, the tail masked.  SAME (u = v): the second product is minus the
+// conjugate of the first one with the columns exchanged, so the sum is twice
+// the real part of the first.
+//
+// Bound: HBM, 3 b0 Nv^2 complex of Gb per coarse site (287 MB on 48 x 24^3,
+// Nv = 24).  Two pieces of 12 columns there: 1.14 ms with the Nv x Nv products
+// spread over lanes and summed by shuffles per term, 0.51 ms here.
+template <int NCS, bool SAME, int RT>
+__global__ __launch_bounds__(256) void k_coarse_slice_part(Geo g, int Nv, int nchunk, int nsrc, int npn, int pair0,
+                                                           const double2* __restrict__ G1, PairSet P, double scale,
                                                            double2* __restrict__ part) {
-    const int x0 = blockIdx.x / nchunk, ch = blockIdx.x - x0 * nchunk;
-    const int n = blockIdx.y, p = blockIdx.z;
-    const int b0 = g.b[0], y0 = x0 / b0, t = x0 - y0 * b0;
-    const int rowsz = g.V1 / g.L1[0];
+    typedef Mfma<double>::v4 V4;
+    constexpr int NCOL = 4 * NCS, GPT = 16 / NCOL;
+    __shared__ double2 red[4][16];
+    int item, tile;
+    if (!site_tile(g.L1[0] * nchunk, (npn + GPT - 1) / GPT, &item, &tile)) return;
+    const int y0 = item / nchunk, ch = item - y0 * nchunk;
+    const int b0 = g.b[0], rowsz = g.V1 / g.L1[0];
     const int ys0 = (int)((long)rowsz * ch / nchunk), ys1 = (int)((long)rowsz * (ch + 1) / nchunk);
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4;
     const int nc = 2 * Nv;
-    const size_t V1 = g.V1;
-    const double2* ci = P.pi[p] + (size_t)n * ncol * V1 * nc;
-    const double2* cj = P.pj[p] + (size_t)n * ncol * V1 * nc;
-    double re = 0.0, im = 0.0;
-    for (int ys = ys0 + w; ys < ys1; ys += 4) {
-        const int y = y0 * rowsz + ys;
-        for (int q = 0; q < T.n; ++q) {
-            const Term tm = T.t[q];
-            const double2* Gb = G1 + (((size_t)y * b0 + t) * 3 + (tm.k - 1)) * Nv * Nv;
-            const double2* u = cj + ((size_t)tm.b * V1 + y) * nc;
-            const double2* v = ci + ((size_t)tm.a * V1 + y) * nc;
-            // u^+ Gamma v = u0^+ Gb v1 - conj(v0^+ Gb u1), lane share
-            cx<double> s1 = cmk(0.0, 0.0), s2 = cmk(0.0, 0.0);
-            for (int cd = lane; cd < Nv * Nv; cd += 64) {
-                const int c = cd / Nv, d = cd - c * Nv;
-                const cx<double> gcd = ldc<double2, double>(Gb + cd);
-                cjmac(s1, ldc<double2, double>(u + c), gcd * ldc<double2, double>(v + Nv + d));
-                cjmac(s2, ldc<double2, double>(v + c), gcd * ldc<double2, double>(u + Nv + d));
+    const size_t V1 = g.V1, nn = (size_t)Nv * Nv;
+    const int nsub = b0 >= 4 ? 1 : 4 / b0;       // wavefronts per time slice
+    const int sub = b0 >= 4 ? 0 : w / b0;
+    // column lr of the tile: group (piece, source) tile * GPT + lr / NCOL, source column a
+    const int pn = tile * GPT + lr / NCOL, a = lr % NCOL;
+    const bool con = lr < GPT * NCOL && pn < npn;
+    const int p = con ? pn / nsrc : 0, n = con ? pn - p * nsrc : 0;
+    const int sa = a / NCS, sc = a - sa * NCS;
+    const double2* vi = P.pi[p] + (size_t)n * NCOL * V1 * nc;
+    const double2* vj = P.pj[p] + (size_t)n * NCOL * V1 * nc;
+    const double2* va = vi + (size_t)a * V1 * nc;
+    for (int t0 = 0; t0 < b0; t0 += 4) {
+        const int t = b0 >= 4 ? t0 + w : w % b0;
+        double re = 0.0, im = 0.0;
+        if (t < b0 && sub < nsub) {
+            for (int ys = ys0 + sub; ys < ys1; ys += nsub) {
+                const int y = y0 * rowsz + ys;
+                const double2* v1 = va + (size_t)y * nc + Nv;
+                for (int k = 1; k <= 3; ++k) {
+                    const int sb = k < 3 ? 3 - sa : sa ^ 2;
+                    const size_t boff = ((size_t)(sb * NCS + sc) * V1 + y) * nc;
+                    const double2* Gb = G1 + (((size_t)y * b0 + t) * 3 + (k - 1)) * nn;
+                    V4 cr[RT], ci[RT], dr[SAME ? 1 : RT], di[SAME ? 1 : RT];
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt) {
+                        cr[rt] = ci[rt] = V4{0, 0, 0, 0};
+                        if (!SAME) dr[rt] = di[rt] = V4{0, 0, 0, 0};
+                    }
+#pragma unroll 2
+                    for (int d0 = 0; d0 < Nv; d0 += 4) {
+                        const int d = d0 + lq;
+                        const bool dok = d < Nv;
+                        const double2 z = make_double2(0.0, 0.0);
+                        const double2 b = (dok && con) ? v1[d] : z;
+                        const double2 b2 = (!SAME && dok && con) ? vj[boff + Nv + d] : z;
+#pragma unroll
+                        for (int rt = 0; rt < RT; ++rt) {
+                            const int c = 16 * rt + lr;
+                            const double2 ga = (dok && c < Nv) ? Gb[(size_t)c * Nv + d] : z;
+                            cr[rt] = Mfma<double>::mac(ga.x, b.x, cr[rt]);
+                            cr[rt] = Mfma<double>::mac(-ga.y, b.y, cr[rt]);
+                            ci[rt] = Mfma<double>::mac(ga.x, b.y, ci[rt]);
+                            ci[rt] = Mfma<double>::mac(ga.y, b.x, ci[rt]);
+                            if (!SAME) {
+                                dr[rt] = Mfma<double>::mac(ga.x, b2.x, dr[rt]);
+                                dr[rt] = Mfma<double>::mac(-ga.y, b2.y, dr[rt]);
+                                di[rt] = Mfma<double>::mac(ga.x, b2.y, di[rt]);
+                                di[rt] = Mfma<double>::mac(ga.y, b2.x, di[rt]);
+                            }
+                        }
+                    }
+                    // x = u_0^+ T (- conj(v_0^+ T_u)) over this lane's rows, times G_k[sa][sb]
+                    cx<double> x = cmk(0.0, 0.0), x2 = cmk(0.0, 0.0);
+                    if (con) {
+#pragma unroll
+                        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) {
+                                const int c = 16 * rt + Mfma<double>::row(lq, r);
+                                if (c < Nv) {
+                                    cjmac(x, ldc<double2, double>(vj + boff + c), cmk(cr[rt][r], ci[rt][r]));
+                                    if (!SAME)
+                                        cjmac(x2, ldc<double2, double>(va + (size_t)y * nc + c),
+                                              cmk(dr[rt][r], di[rt][r]));
+                                }
+                            }
+                    }
+                    int tc;
+                    double wr, wi;
+                    gk_row(k, sa, &tc, &wr, &wi);
+                    const cx<double> f = SAME ? cmk(2.0 * (wr * x.re - wi * x.im), 0.0) : cmk(wr, wi) * (x - conj(x2));
+                    re += f.re;
+                    im += SAME ? 0.0 * f.re : f.im;
+                }
             }
-            const cx<double> val = cmk(tm.cre, tm.cim) * (s1 - conj(s2));
-            re += val.re;
-            im += val.im;
         }
+        // rows (the four lanes of a column), then the columns of a group and
+        // the wavefronts of a time slice, all in a fixed order
+        re += __shfl_xor(re, 16, 64); im += __shfl_xor(im, 16, 64);
+        re += __shfl_xor(re, 32, 64); im += __shfl_xor(im, 32, 64);
+        if (lq == 0) red[w][lr] = make_double2(re, im);
+        __syncthreads();
+        const int nt = b0 - t0 < 4 ? b0 - t0 : 4;
+        if ((int)threadIdx.x < nt * GPT) {
+            const int tt = threadIdx.x / GPT, gq = threadIdx.x - tt * GPT, pg = tile * GPT + gq;
+            if (pg < npn) {
+                double sr = 0.0, si = 0.0;
+                for (int s = 0; s < nsub; ++s)
+                    for (int cc = 0; cc < NCOL; ++cc) {
+                        const double2 v = red[tt + s * b0][gq * NCOL + cc];
+                        sr += v.x;
+                        si += v.y;
+                    }
+                const int pp = pg / nsrc, ns = pg - pp * nsrc, x0 = y0 * b0 + t0 + tt;
+                part[((((size_t)(pair0 + pp) * nsrc + ns) * g.L[0] + x0) * LV_MAXCHUNK) + ch] =
+                    make_double2(scale * sr, scale * si);
+            }
+        }
+        __syncthreads();
     }
-    const double2 v = wg_sum256(re, im);
-    if (threadIdx.x == 0)
-        part[((((size_t)(pair0 + p) * nsrc + n) * g.L[0] + x0) * LV_MAXCHUNK) + ch] = v;
 }
 
 // out[row][t] (+)= (1/ntot) sum_n [S(row, n, x_n) - diff * S(row + 1, n, x_n)],
@@ -417,16 +320,20 @@ __global__ void k_levels_finish(int L0, int nrow, int npair, int nsrc, int diff,
     out[e] = o;
 }
 
-// Partials of every pair for sources [0, nsrc) of the given pieces into part
-// (npair * nsrc * L0 * LV_MAXCHUNK complex) and the chunk counts.
-static int slice_partials(mglma_ctx* c, const TermList& T, int ncol, int nsrc, int nfine, int npair,
-                          const PairSet& P, double2* part, PairChunks* pc) {
+struct SrcKind {
+    int ncs;        // source colours: 3 (point) or 1 (wall)
+    double scale;
+};
+
+template <int NCS, bool SAME>
+static int slice_partials_k(mglma_ctx* c, double scale, int nsrc, int nfine, int npair, const PairSet& P,
+                            double2* part, PairChunks* pc) {
     const Geo& g = c->geo;
     const int nchf = fine_chunks(g), nchc = coarse_chunks(g);
     for (int p = 0; p < npair; ++p) pc->nch[p] = p < nfine ? nchf : nchc;
     if (nfine > 0) {
-        hipLaunchKernelGGL(k_fine_slice_part, dim3(g.L[0] * nchf, nsrc, nfine), dim3(256), 0, c->stream, g, nchf,
-                           ncol, nsrc, 0, P, T, part);
+        hipLaunchKernelGGL((k_fine_slice_part<NCS, SAME>), dim3(g.L[0] * nchf, nsrc, nfine), dim3(256), 0, c->stream,
+                           g, nchf, nsrc, 0, P, scale, part);
         HIP_TRY(hipGetLastError());
     }
     if (npair > nfine) {
@@ -435,31 +342,55 @@ static int slice_partials(mglma_ctx* c, const TermList& T, int ncol, int nsrc, i
             Q.pi[p] = p + nfine < LV_MAXPAIR ? P.pi[p + nfine] : nullptr;
             Q.pj[p] = p + nfine < LV_MAXPAIR ? P.pj[p + nfine] : nullptr;
         }
-        hipLaunchKernelGGL(k_coarse_slice_part, dim3(g.L[0] * nchc, nsrc, npair - nfine), dim3(256), 0, c->stream, g,
-                           c->Nv, nchc, ncol, nsrc, nfine, (const double2*)c->G1, Q, T, part);
+        constexpr int GPT = 16 / (4 * NCS);
+        const int npn = (npair - nfine) * nsrc;
+        const dim3 grid(site_tile_grid((long)g.L1[0] * nchc, (npn + GPT - 1) / GPT));
+#define LV_COARSE(RT)                                                                                          \
+    hipLaunchKernelGGL((k_coarse_slice_part<NCS, SAME, RT>), grid, dim3(256), 0, c->stream, g, c->Nv, nchc, nsrc, \
+                       npn, nfine, (const double2*)c->G1, Q, scale, part)
+        switch ((c->Nv + 15) / 16) {
+            case 1: LV_COARSE(1); break;
+            case 2: LV_COARSE(2); break;
+            case 3: LV_COARSE(3); break;
+            default: LV_COARSE(4); break;
+        }
+#undef LV_COARSE
         HIP_TRY(hipGetLastError());
     }
     return MGLMA_OK;
 }
 
-static int check_sources(mglma_ctx* c, int kind, int nsrc, const int* t_src, TermList* T, int* ncol) {
+// Partials of every pair for sources [0, nsrc) of the given pieces into part
+// (npair * nsrc * L0 * LV_MAXCHUNK complex) and the chunk counts.
+static int slice_partials(mglma_ctx* c, const SrcKind& K, int nsrc, int nfine, int npair, const PairSet& P,
+                          double2* part, PairChunks* pc) {
+    bool same = true;
+    for (int p = 0; p < npair; ++p) same = same && P.pi[p] == P.pj[p];
+    if (K.ncs == 3)
+        return same ? slice_partials_k<3, true>(c, K.scale, nsrc, nfine, npair, P, part, pc)
+                    : slice_partials_k<3, false>(c, K.scale, nsrc, nfine, npair, P, part, pc);
+    return same ? slice_partials_k<1, true>(c, K.scale, nsrc, nfine, npair, P, part, pc)
+                : slice_partials_k<1, false>(c, K.scale, nsrc, nfine, npair, P, part, pc);
+}
+
+static int check_sources(mglma_ctx* c, int kind, int nsrc, const int* t_src, SrcKind* K) {
     if (kind != MGLMA_SRC_POINT && kind != MGLMA_SRC_STOCH) return MGLMA_ERR_ARG;
     if (nsrc < 1 || nsrc > LV_MAXSRC || !t_src) return MGLMA_ERR_ARG;
     for (int n = 0; n < nsrc; ++n)
         if (t_src[n] < 0 || t_src[n] >= c->L[0]) return MGLMA_ERR_ARG;
-    *T = kind == MGLMA_SRC_POINT ? point_terms() : stoch_terms((double)c->geo.V3);
-    *ncol = kind == MGLMA_SRC_POINT ? 12 : 4;
+    K->ncs = kind == MGLMA_SRC_POINT ? 3 : 1;
+    K->scale = kind == MGLMA_SRC_POINT ? 1.0 / 3.0 : 1.0 / (3.0 * c->geo.V3);
     return MGLMA_OK;
 }
 
 // Shared body of mglma_contract_levels and its allocation-free variant:
 // part holds at least npair * nsb * L0 * LV_MAXCHUNK complex, out_dev the
 // nrow * L0 result; sources are processed nsb at a time.
-static int levels_body(mglma_ctx* c, const TermList& T, int ncol, int nsrc, const int* t_src, int nfine, int npair,
+static int levels_body(mglma_ctx* c, const SrcKind& K, int nsrc, const int* t_src, int nfine, int npair,
                        const PairSet& P, int diff, int nrow, int nsb, double2* part, double2* out_dev,
                        double scale = 0.0, int accumulate = 0) {
     if (scale == 0.0) scale = 1.0 / nsrc;
-    const int L0 = c->L[0];
+    const int L0 = c->L[0], ncol = 4 * K.ncs;
     for (int n0 = 0; n0 < nsrc; n0 += nsb) {
         const int nb = nsrc - n0 < nsb ? nsrc - n0 : nsb;
         PairSet Pn;
@@ -470,7 +401,7 @@ static int levels_body(mglma_ctx* c, const TermList& T, int ncol, int nsrc, cons
             Pn.pj[p] = p < npair ? P.pj[p] + off : nullptr;
         }
         PairChunks pc;
-        MG_TRY(slice_partials(c, T, ncol, nb, nfine, npair, Pn, part, &pc));
+        MG_TRY(slice_partials(c, K, nb, nfine, npair, Pn, part, &pc));
         SrcTimes ts;
         for (int n = 0; n < nb; ++n) ts.t[n] = t_src[n0 + n];
         hipLaunchKernelGGL(k_levels_finish, dim3((nrow * L0 + 127) / 128), dim3(128), 0, c->stream, L0, nrow, npair,
@@ -482,10 +413,10 @@ static int levels_body(mglma_ctx* c, const TermList& T, int ncol, int nsrc, cons
 }
 
 static int levels_args(mglma_ctx* c, int kind, int nsrc, const int* t_src, const double* fine, int ncoarse,
-                       const double* const* coarse, int exact_top, double* G_host, TermList* T, int* ncol,
+                       const double* const* coarse, int exact_top, double* G_host, SrcKind* K,
                        PairSet* P, int* nfine, int* npair) {
     if (!c || !G_host || ncoarse < 0 || (ncoarse > 0 && !coarse)) return MGLMA_ERR_ARG;
-    MG_TRY(check_sources(c, kind, nsrc, t_src, T, ncol));
+    MG_TRY(check_sources(c, kind, nsrc, t_src, K));
     *nfine = fine ? 1 : 0;
     *npair = *nfine + ncoarse;
     if (*npair < 1 || *npair > LV_MAXPAIR) return MGLMA_ERR_ARG;
@@ -502,16 +433,15 @@ static int levels_args(mglma_ctx* c, int kind, int nsrc, const int* t_src, const
 
 extern "C" int mglma_contract_levels(mglma_ctx* c, int kind, int nsrc, const int* t_src, const double* fine,
                                      int ncoarse, const double* const* coarse, int exact_top, double* G_host) {
-    TermList T;
+    SrcKind K;
     PairSet P;
-    int ncol, nfine, npair;
-    MG_TRY(levels_args(c, kind, nsrc, t_src, fine, ncoarse, coarse, exact_top, G_host, &T, &ncol, &P, &nfine,
-                       &npair));
+    int nfine, npair;
+    MG_TRY(levels_args(c, kind, nsrc, t_src, fine, ncoarse, coarse, exact_top, G_host, &K, &P, &nfine, &npair));
     const int L0 = c->L[0], nrow = npair + (exact_top ? 1 : 0);
     double2 *part, *out;
     MG_TRY(mg_scratch(c, 28, (size_t)npair * nsrc * L0 * LV_MAXCHUNK * 16, (void**)&part));
     MG_TRY(mg_scratch(c, 29, (size_t)nrow * L0 * 16 + 256, (void**)&out));
-    MG_TRY(levels_body(c, T, ncol, nsrc, t_src, nfine, npair, P, 1, npair, nsrc, part, out));
+    MG_TRY(levels_body(c, K, nsrc, t_src, nfine, npair, P, 1, npair, nsrc, part, out));
     if (exact_top) MG_TRY(mg_top_corr(c, out + (size_t)npair * L0));
     HIP_TRY(hipMemcpyAsync(G_host, out, (size_t)nrow * L0 * 16, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
@@ -522,25 +452,24 @@ extern "C" int mglma_contract_levels_acc(mglma_ctx* c, int kind, int nsrc, const
                                          int ncoarse, const double* const* coarse, double weight, int accumulate,
                                          double* G_dev) {
     if (!G_dev || !(weight == weight)) return MGLMA_ERR_ARG;
-    TermList T;
+    SrcKind K;
     PairSet P;
-    int ncol, nfine, npair;
+    int nfine, npair;
     double dummy;
-    MG_TRY(levels_args(c, kind, nsrc, t_src, fine, ncoarse, coarse, 0, &dummy, &T, &ncol, &P, &nfine, &npair));
+    MG_TRY(levels_args(c, kind, nsrc, t_src, fine, ncoarse, coarse, 0, &dummy, &K, &P, &nfine, &npair));
     if (weight == 0.0) return MGLMA_ERR_ARG;
     const int L0 = c->L[0];
     double2* part;
     MG_TRY(mg_scratch(c, 28, (size_t)npair * nsrc * L0 * LV_MAXCHUNK * 16, (void**)&part));
-    return levels_body(c, T, ncol, nsrc, t_src, nfine, npair, P, 1, npair, nsrc, part, (double2*)G_dev, weight,
+    return levels_body(c, K, nsrc, t_src, nfine, npair, P, 1, npair, nsrc, part, (double2*)G_dev, weight,
                        accumulate ? 1 : 0);
 }
 
 extern "C" int mglma_contract_pair(mglma_ctx* c, int kind, int nsrc, const int* t_src, int coarse,
                                    const double* psi_i, const double* psi_j, double* G_host) {
     if (!c || !psi_i || !psi_j || !G_host || (coarse != 0 && coarse != 1)) return MGLMA_ERR_ARG;
-    TermList T;
-    int ncol;
-    MG_TRY(check_sources(c, kind, nsrc, t_src, &T, &ncol));
+    SrcKind K;
+    MG_TRY(check_sources(c, kind, nsrc, t_src, &K));
     if (coarse && !c->have_subspace) return MGLMA_ERR_NO_SUBSPACE;
     PairSet P;
     for (int p = 0; p < LV_MAXPAIR; ++p) P.pi[p] = P.pj[p] = nullptr;
@@ -550,10 +479,32 @@ extern "C" int mglma_contract_pair(mglma_ctx* c, int kind, int nsrc, const int* 
     double2 *part, *out;
     MG_TRY(mg_scratch(c, 28, (size_t)nsrc * L0 * LV_MAXCHUNK * 16, (void**)&part));
     MG_TRY(mg_scratch(c, 29, (size_t)L0 * 16 + 256, (void**)&out));
-    MG_TRY(levels_body(c, T, ncol, nsrc, t_src, coarse ? 0 : 1, 1, P, 0, 1, nsrc, part, out));
+    MG_TRY(levels_body(c, K, nsrc, t_src, coarse ? 0 : 1, 1, P, 0, 1, nsrc, part, out));
     HIP_TRY(hipMemcpyAsync(G_host, out, (size_t)L0 * 16, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     return MGLMA_OK;
+}
+
+// one source: the same two-point function (entry t of its row is C(t0 + t, t0))
+static int contract_one(mglma_ctx* c, int kind, int coarse, const double* pi, const double* pj, int t0, double* C) {
+    if (!c || !pi || !pj || !C || t0 < 0 || t0 >= c->L[0]) return MGLMA_ERR_ARG;
+    return mglma_contract_pair(c, kind, 1, &t0, coarse, pi, pj, C);
+}
+
+extern "C" int mglma_contract_point(mglma_ctx* c, const double* pi, const double* pj, int y0, double* C) {
+    return contract_one(c, MGLMA_SRC_POINT, 0, pi, pj, y0, C);
+}
+
+extern "C" int mglma_contract_point_coarse(mglma_ctx* c, const double* ci, const double* cj, int y0, double* C) {
+    return contract_one(c, MGLMA_SRC_POINT, 1, ci, cj, y0, C);
+}
+
+extern "C" int mglma_contract_stoch(mglma_ctx* c, const double* pi, const double* pj, int tn, double* C) {
+    return contract_one(c, MGLMA_SRC_STOCH, 0, pi, pj, tn, C);
+}
+
+extern "C" int mglma_contract_stoch_coarse(mglma_ctx* c, const double* ci, const double* cj, int tn, double* C) {
+    return contract_one(c, MGLMA_SRC_STOCH, 1, ci, cj, tn, C);
 }
 
 // ---------------------------------------------------------------------------
@@ -583,10 +534,10 @@ int mg_noalloc_init(int device) {
 extern "C" int mglma_contract_levels_noalloc(mglma_ctx* c, int kind, int nsrc, const int* t_src,
                                              const double* fine, int ncoarse, const double* const* coarse,
                                              double* G_host) {
-    TermList T;
+    SrcKind K;
     PairSet P;
-    int ncol, nfine, npair;
-    MG_TRY(levels_args(c, kind, nsrc, t_src, fine, ncoarse, coarse, 0, G_host, &T, &ncol, &P, &nfine, &npair));
+    int nfine, npair;
+    MG_TRY(levels_args(c, kind, nsrc, t_src, fine, ncoarse, coarse, 0, G_host, &K, &P, &nfine, &npair));
     if (c->device < 0 || c->device >= NOALLOC_MAXDEV) return MGLMA_ERR_ARG;
     double2* base;
     {
@@ -603,7 +554,7 @@ extern "C" int mglma_contract_levels_noalloc(mglma_ctx* c, int kind, int nsrc, c
     if (nsb > (size_t)nsrc) nsb = (size_t)nsrc;
     double2* out = base;
     double2* part = base + out_n;
-    MG_TRY(levels_body(c, T, ncol, nsrc, t_src, nfine, npair, P, 1, nrow, (int)nsb, part, out));
+    MG_TRY(levels_body(c, K, nsrc, t_src, nfine, npair, P, 1, nrow, (int)nsb, part, out));
     HIP_TRY(hipMemcpyAsync(G_host, out, (size_t)nrow * L0 * 16, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     return MGLMA_OK;
