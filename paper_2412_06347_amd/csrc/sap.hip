@@ -158,7 +158,7 @@ __device__ __forceinline__ void sap_hop_block_h(const Geo& g, int blk, int l, co
             }
             o[sp * 3 + a] = cmk(re, im);
         }
-    recon_h<MU, FWD>(acc, o, neg ? -1.f : 1.f);
+    reconstruct_sg<MU, FWD, float>(acc, o, neg ? -1.f : 1.f);
     __builtin_amdgcn_sched_barrier(0);
 }
 

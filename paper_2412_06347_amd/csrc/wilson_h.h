@@ -6,7 +6,7 @@
 // accumulator.  Links, clover and spinors are never unpacked; all sums over
 // colour, spin and hops are FP32.
 #pragma once
-#include "mglma_internal.h"
+#include "wilson.h"
 
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 
@@ -46,24 +46,6 @@ __device__ __forceinline__ void proj_h(const h2 p[12], h2 h[6]) {
     for (int a = 0; a < 3; ++a) {
         h[a] = proj_f<F, I, S0>(p[a], p[3 * Q0 + a]);
         h[3 + a] = proj_f<F, I, S1>(p[3 + a], p[3 * Q1 + a]);
-    }
-}
-
-// acc += sg * (full spinor reconstructed from the link-multiplied half spinor o)
-template <int MU, bool FWD>
-__device__ __forceinline__ void recon_h(cx<float> acc[12], const cx<float> o[6], float sg) {
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const cx<float> h0 = o[a], h1 = o[3 + a];
-        cx<float> l2, l3;
-        if (MU == 0) { l2 = FWD ? h0 : -h0; l3 = FWD ? h1 : -h1; }
-        else if (MU == 1) { l2 = FWD ? mul_mi(h1) : mul_i(h1); l3 = FWD ? mul_mi(h0) : mul_i(h0); }
-        else if (MU == 2) { l2 = FWD ? -h1 : h1; l3 = FWD ? h0 : -h0; }
-        else { l2 = FWD ? mul_mi(h0) : mul_i(h0); l3 = FWD ? mul_i(h1) : mul_mi(h1); }
-        acc[a].re = fmaf(sg, h0.re, acc[a].re); acc[a].im = fmaf(sg, h0.im, acc[a].im);
-        acc[3 + a].re = fmaf(sg, h1.re, acc[3 + a].re); acc[3 + a].im = fmaf(sg, h1.im, acc[3 + a].im);
-        acc[6 + a].re = fmaf(sg, l2.re, acc[6 + a].re); acc[6 + a].im = fmaf(sg, l2.im, acc[6 + a].im);
-        acc[9 + a].re = fmaf(sg, l3.re, acc[9 + a].re); acc[9 + a].im = fmaf(sg, l3.im, acc[9 + a].im);
     }
 }
 

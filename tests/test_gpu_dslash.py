@@ -97,6 +97,55 @@ def test_apply_f16_batches(nrhs):
             assert err < 2e-3
 
 
+@pytest.mark.parametrize("nrhs", [2, 3, 4, 5, 9, 13])
+@pytest.mark.parametrize("L,b", [((4, 3, 3, 3), (2, 3, 3, 1)), ((8, 4, 4, 4), (4, 4, 4, 4)), ((3, 5, 3, 3), (3, 5, 3, 3))],
+                         ids=["tail_tile", "tile_is_slice", "one_block"])
+def test_apply_batch_tiles(L, b, nrhs):
+    """Batches run in tiles of 64 sites with the neighbours inside a tile taken
+    from its lanes: a ragged last tile, tiles that are whole block slices, tiles
+    across slices of a block that spans the lattice; batches around the rounds
+    of four right-hand sides.  Tolerances: those of test_apply_parity."""
+    import torch
+    from paper_2412_06347_amd import mglma
+    ctx, U = _ctx(L, b, 0.124, 1.0, 0.3, seed=5)
+    D = dirac.WilsonClover(U, L, 0.124, 1.0)
+    psi = synth.gaussian_fields(nrhs, L, seed=31)
+    ref = D.M_canon(dirac.fields_to_lattice(psi, L))
+    for prec, tol in [(mglma.F64, 1e-12), (mglma.F32, 2e-6), (mglma.F16, 2e-3)]:
+        x, y = ctx.fine(nrhs, prec), ctx.fine(nrhs, prec)
+        ctx.import_fields(to_dev(psi), x, prec)
+        ctx.apply_D(x, y, prec)
+        out = torch.empty((nrhs, ctx.V, 4, 3, 2), dtype=torch.float64, device="cuda")
+        ctx.export_fields(y, out, prec)
+        assert relerr(from_dev(out), ref) < tol
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2], ids=["f64", "f32", "f16"])
+def test_apply_batch_repeats(prec):
+    """A full-size batch gives the values of one right-hand side at a time in
+    every pass (FP64 and FP32 sum in the same order: equal to a few rounding
+    errors; FP16 batches compute on packed data), and the same bits each time."""
+    import torch
+    from paper_2412_06347_amd import mglma
+    L, nrhs = (48, 24, 24, 24), 12
+    ctx = mglma.Context(L, (4, 4, 4, 4), 0.124, 1.0)
+    g = torch.Generator(device="cuda").manual_seed(9)
+    U = torch.linalg.qr(torch.randn((ctx.V * 4, 3, 3), generator=g, device="cuda", dtype=torch.complex64))[0]
+    ctx.load_gauge(torch.view_as_real(U.to(torch.complex128)).contiguous())
+    x, y, ref = ctx.fine(nrhs, prec), ctx.fine(nrhs, prec), ctx.fine(nrhs, prec)
+    x.copy_(torch.randn(x.shape, generator=g, device="cuda", dtype=torch.float32))
+    for q in range(nrhs):
+        ctx.apply_D(x[q:q + 1], ref[q:q + 1], prec)
+    first = None
+    for _ in range(8):
+        y.zero_()
+        ctx.apply_D(x, y, prec)
+        err = float((y.float() - ref.float()).abs().max())
+        assert err <= (1e-5, 1e-4, 0.25)[prec], err
+        first = y.clone() if first is None else first
+        assert torch.equal(y, first)
+
+
 def test_import_export_roundtrip():
     import torch
     from paper_2412_06347_amd import mglma
