@@ -132,14 +132,14 @@ __global__ __launch_bounds__(256, W) void k_dslash_tile(Geo g, const S* __restri
     tile_stage_gauge<CL, G>(g, i, lc, yc, U, C, ul, w, nw, lane);
     __syncthreads();
     const uint32_t vc = g.V;
+    const int i0 = tile * TILE;
     for (int q = (pos - tl * ng) * nw + w; q < nrhs; q += ng * nw) {
         const FieldRsrc pr = field_rsrc(in + q * 12 * V, vc);
         const uint32_t io = opaque_v((uint32_t)i);
         cx<R> acc[12], own[12];
-#pragma unroll
-        for (int k = 0; k < 12; ++k) own[k] = buf_ldc<S, R>(pr.half[k / 6], io, k % 6 * vc);
+        tile_own<S, R>(pr, io, vc, own);
         const int lo = (int)opaque_v(lane);
-        tile_hops<S, G, R>(g, i, tile * TILE, lc, yc, pr, own, ul, lo, acc);
+        tile_hops<S, G, R>(g, i, i0, lc, yc, pr, own, ul, lo, acc);
         const R isc = RESID ? (R)(1.0 / scale[q]) : (R)1;
 #pragma unroll
         for (int ch = 0; ch < 2; ++ch) {
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(256, W) void k_dslash_tile(Geo g, const S* __restri
             for (int k = 0; k < 6; ++k) {
                 cx<R> v = res[k] - kappa * acc[6 * ch + k];
                 if (gamma5 && ch == 1) v = -v;
-                if (RESID) v = isc * (buf_ldc<S, R>(six_rsrc(rsub + q * 12 * V, 6 * ch, vc), io, k * vc) - v);
+                if (RESID) v = isc * (buf_ldc<S, R>(comp_rsrc(rsub + q * 12 * V, 6 * ch + k, 1, vc), io, 0) - v);
                 buf_stc<SO, R>(out + q * 12 * V, vc, io, 6 * ch + k, v);
             }
         }
@@ -168,7 +168,7 @@ __device__ __forceinline__ void hop_h(const Geo& g, int i, int i0, const int lc[
     const Nbr n = tile_nbr<MU, FWD>(g, i, i0, lc, yc, 4u);
     h2 p[12], h[6], hl[6];
 #pragma unroll
-    for (int sc = 0; sc < 12; ++sc) p[sc] = buf_ld<h2>(pin.half[sc / 6], n.off, (sc % 6) * V * 4u);
+    for (int sc = 0; sc < 12; ++sc) p[sc] = buf_ld<h2>(pin.part[sc / 2], n.off, (sc % 2) * V * 4u);
     proj_h<MU, FWD, FZ>(own, h);
 #pragma unroll
     for (int k = 0; k < 6; ++k) h[k] = __builtin_bit_cast(h2, lane_get(__builtin_bit_cast(int, h[k]), n.src));
@@ -208,8 +208,9 @@ __global__ __launch_bounds__(256, 4) void k_dslash_h(Geo g, const h2* __restrict
     const int bid = blockIdx.x, pos = bid >> 3, tl = pos / ng;
     const int tile = (bid & 7) * (ntp >> 3) + tl;
     if (tile * TILE >= g.V) return;
-    const int w = wave_id(), nw = blockDim.x >> 6, lane = threadIdx.x & 63, i0 = tile * TILE;
-    const int i = i0 + lane < g.V ? i0 + lane : g.V - 1;
+    const int w = wave_id(), nw = blockDim.x >> 6, lane = threadIdx.x & 63;
+    const int i = tile * TILE + lane < g.V ? tile * TILE + lane : g.V - 1;
+    const int i0 = tile * TILE;
     const uint32_t V = g.V;
     int lc[4], yc[4];
     geo_coords(g, i, lc, yc);
@@ -223,7 +224,7 @@ __global__ __launch_bounds__(256, 4) void k_dslash_h(Geo g, const h2* __restrict
         h2 own[12];
 #pragma unroll
         for (int k = 0; k < 12; ++k) {
-            own[k] = buf_ld<h2>(pin.half[k / 6], io, k % 6 * V * 4u);
+            own[k] = buf_ld<h2>(pin.part[k / 2], io, k % 2 * V * 4u);
             acc[k] = cmk(0.f, 0.f);
         }
         hop_h<0, true>(g, i, i0, lc, yc, pin, own, ul, lo, acc);
@@ -244,7 +245,7 @@ __global__ __launch_bounds__(256, 4) void k_dslash_h(Geo g, const h2* __restrict
                 res[0][k] = -kappa * acc[6 * ch + k];
             }
             clover_dot2<1>([&](int k) { return CL ? ul[(72 + ch * 18 + k) * TILE + lo]
-                                                  : buf_ld<h2>(six_rsrc(C, ch * 18 + k / 6 * 6, V), io, k % 6 * V * 4u); },
+                                                  : buf_ld<h2>(comp_rsrc(C, ch * 18 + k / 3 * 3, 3, V), io, k % 3 * V * 4u); },
                            p, res);
 #pragma unroll
             for (int k = 0; k < 6; ++k) {
@@ -255,25 +256,6 @@ __global__ __launch_bounds__(256, 4) void k_dslash_h(Geo g, const h2* __restrict
         }
     }
 }
-
-// Launch shape of a batch of nrhs right-hand sides: tiles padded to a multiple
-// of the XCD count, and ng workgroups per tile, back to back on one XCD, that
-// share the right-hand sides.  One workgroup stages a tile's links once for
-// the whole batch; where the tiles alone leave the chip idle (fewer than two
-// workgroups per compute unit) the rounds of four right-hand sides are dealt
-// to several.
-struct TileGrid {
-    int nt, ng;
-    dim3 grid, block;
-    TileGrid(int V, int nrhs) {
-        const int rounds = (nrhs + 3) / 4;
-        nt = ((V + TILE - 1) / TILE + 7) / 8 * 8;
-        ng = nt >= 512 ? 1 : (512 + nt - 1) / nt;
-        if (ng > rounds) ng = rounds;
-        grid = dim3((unsigned)nt * ng);
-        block = dim3(64 * ((nrhs + rounds - 1) / rounds));
-    }
-};
 
 int mg_dslash(mglma_ctx* c, int prec, int gamma5, const void* in, void* out, int nrhs) {
     if (nrhs == 0) return MGLMA_OK;

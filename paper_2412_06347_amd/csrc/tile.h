@@ -1,5 +1,5 @@
-// Wilson hops of a tile of 64 sites for a batch of right-hand sides, shared by
-// the operator kernels and the SAP residual.
+// Wilson hops of a tile of 64 sites for a batch of right-hand sides, and the
+// buffer accesses they share with the SAP kernel.
 //
 // A workgroup owns 64 consecutive sites (lane = site) and its wavefronts walk
 // the right-hand sides, one per wavefront at a time.  The tile's eight links
@@ -16,6 +16,25 @@ __host__ __device__ constexpr int tile_gauge(bool CL) { return (CL ? 108 : 72) *
 
 // the wavefront's index as a scalar (uniform addresses for its right-hand side)
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
+
+// Launch shape of a batch of nrhs right-hand sides: tiles padded to a multiple
+// of the XCD count, and ng workgroups per tile, back to back on one XCD, that
+// share the right-hand sides.  One workgroup stages a tile's links once for
+// the whole batch; where the tiles alone leave the chip idle (fewer than two
+// workgroups per compute unit) the rounds of four right-hand sides are dealt
+// to several.
+struct TileGrid {
+    int nt, ng;
+    dim3 grid, block;
+    TileGrid(int V, int nrhs) {
+        const int rounds = (nrhs + 3) / 4;
+        nt = ((V + TILE - 1) / TILE + 7) / 8 * 8;
+        ng = nt >= 512 ? 1 : (512 + nt - 1) / nt;
+        if (ng > rounds) ng = rounds;
+        grid = dim3((unsigned)nt * ng);
+        block = dim3(64 * ((nrhs + rounds - 1) / rounds));
+    }
+};
 
 // every wavefront copies its share of the tile's links U_mu(x), U_mu(x - mu) and clover term
 template <bool CL, typename G>
@@ -54,7 +73,7 @@ __device__ __forceinline__ int opaque_zero() {
 }
 // Buffer loads and stores: the per-component offset (component x V) is uniform
 // and goes in a scalar register, the site offset is the only vector operand.
-// A resource spans six components, 6 V sizeof(S) < 2^32 bytes (tile_fits).
+// A resource spans a few components, so that its bytes stay below 2^32 (tile_fits).
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 __device__ __forceinline__ rsrc_t mk_rsrc(const void* p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
@@ -79,18 +98,19 @@ template <typename S> __device__ __forceinline__ void buf_st(S* f, uint32_t V, u
     else if constexpr (sizeof(S) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2_t, v), r, off, 0, 0);
     else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4_t, v), r, off, 0, 0);
 }
-// six components of a field from component c0 on
-template <typename S> __device__ __forceinline__ rsrc_t six_rsrc(S* f, int c0, uint32_t V) {
-    return mk_rsrc(f + (size_t)c0 * V, 6u * V * (uint32_t)sizeof(S));
+// components [c0, c0 + n) of a field
+template <typename S> __device__ __forceinline__ rsrc_t comp_rsrc(S* f, int c0, int n, uint32_t V) {
+    return mk_rsrc(f + (size_t)c0 * V, (uint32_t)n * V * (uint32_t)sizeof(S));
 }
-// one right-hand side: the components of the two chiralities
+// one right-hand side, two components a resource
 struct FieldRsrc {
-    rsrc_t half[2];
+    rsrc_t part[6];
 };
 template <typename S> __device__ __forceinline__ FieldRsrc field_rsrc(S* f, uint32_t V) {
-    return {{six_rsrc(f, 0, V), six_rsrc(f, 6, V)}};
+    return {{comp_rsrc(f, 0, 2, V), comp_rsrc(f, 2, 2, V), comp_rsrc(f, 4, 2, V), comp_rsrc(f, 6, 2, V),
+             comp_rsrc(f, 8, 2, V), comp_rsrc(f, 10, 2, V)}};
 }
-static inline bool tile_fits(size_t V, size_t sbytes) { return 6 * V * sbytes < ((size_t)1 << 32); }
+static inline bool tile_fits(size_t V, size_t sbytes) { return 2 * V * sbytes < ((size_t)1 << 32); }
 // entry `comp` V + `site` of a resource, as complex R
 template <typename S, typename R> __device__ __forceinline__ cx<R> buf_ldc(rsrc_t r, uint32_t site, uint32_t comp) {
     const S v = buf_ld<S>(r, site * (uint32_t)sizeof(S), comp * (uint32_t)sizeof(S));
@@ -101,6 +121,12 @@ __device__ __forceinline__ void buf_stc(S* f, uint32_t V, uint32_t site, int com
     S v;
     stc<S, R>(&v, x);
     buf_st<S>(f, V, site, comp, v);
+}
+
+template <typename S, typename R>
+__device__ __forceinline__ void tile_own(const FieldRsrc& pr, uint32_t io, uint32_t V, cx<R> own[12]) {
+#pragma unroll
+    for (int k = 0; k < 12; ++k) own[k] = buf_ldc<S, R>(pr.part[k / 2], io, k % 2 * V);
 }
 
 // value of another lane of the wavefront; src = 4 * lane
@@ -146,7 +172,7 @@ __device__ __forceinline__ void tile_hop(const Geo& g, int i, int i0, const int 
     cx<R> p[12], h[6], hl[6];
 #pragma unroll
     for (int sc = 0; sc < 12; ++sc) {
-        const S v = buf_ld<S>(pr.half[sc / 6], n.off, (sc % 6) * V * (uint32_t)sizeof(S));
+        const S v = buf_ld<S>(pr.part[sc / 2], n.off, (sc % 2) * V * (uint32_t)sizeof(S));
         p[sc] = ldc<S, R>(&v);
     }
     // the projection is the same on every lane: the owner of a neighbour inside
@@ -201,6 +227,6 @@ __device__ __forceinline__ void tile_clover(const G* ul, int lane, const G* C, u
     if (CL)
         clover_apply<R>([&](int k) { return ldc<G, R>(ul + (72 + ch * 18 + k) * TILE + lane); }, p, res);
     else
-        clover_apply<R>([&](int k) { return buf_ldc<G, R>(six_rsrc(C, ch * 18 + k / 6 * 6, V), io, k % 6 * V); }, p,
+        clover_apply<R>([&](int k) { return buf_ldc<G, R>(comp_rsrc(C, ch * 18 + k / 3 * 3, 3, V), io, k % 3 * V); }, p,
                         res);
 }

@@ -130,8 +130,8 @@ def test_apply_batch_repeats(prec):
     L, nrhs = (48, 24, 24, 24), 12
     ctx = mglma.Context(L, (4, 4, 4, 4), 0.124, 1.0)
     g = torch.Generator(device="cuda").manual_seed(9)
-    U = torch.linalg.qr(torch.randn((ctx.V * 4, 3, 3), generator=g, device="cuda", dtype=torch.complex64))[0]
-    ctx.load_gauge(torch.view_as_real(U.to(torch.complex128)).contiguous())
+    # any 3 x 3 matrices do as links here
+    ctx.load_gauge(0.4 * torch.randn((ctx.V, 4, 3, 3, 2), generator=g, device="cuda", dtype=torch.float64))
     x, y, ref = ctx.fine(nrhs, prec), ctx.fine(nrhs, prec), ctx.fine(nrhs, prec)
     x.copy_(torch.randn(x.shape, generator=g, device="cuda", dtype=torch.float32))
     for q in range(nrhs):

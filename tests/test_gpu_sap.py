@@ -47,6 +47,17 @@ def test_sap_cycles_parity(pair, prec, tol):
     assert e < tol
 
 
+# block sizes of 36, 81 and 192 sites: part of one wavefront, two and three wavefronts, with and without wrap-around
+SIZES = [((6, 6, 4, 4), (3, 3, 2, 2)), ((6, 6, 6, 6), (3, 3, 3, 3)), ((8, 4, 4, 6), (4, 4, 4, 3))]
+
+
+@pytest.mark.parametrize("L,b", SIZES, ids=["36", "81", "192_ext1"])
+@pytest.mark.parametrize("prec,tol", [(1, 2e-6), (2, 5e-3)], ids=["f32", "f16"])
+def test_sap_block_sizes(L, b, prec, tol):
+    """A workgroup has as many wavefronts as the block needs; its idle threads stay out of the block's sums."""
+    test_sap_cycles_parity(Pair(L, b, 2, kappa=0.124, oracle_galerkin=False), prec, tol)
+
+
 @pytest.mark.parametrize("scale", [1e-7, 1e3])
 def test_sap_cycles_parity_scaled(pair, scale):
     """FP16 links at right-hand sides far from unit scale (entries around
