@@ -166,282 +166,266 @@ __global__ __launch_bounds__(256) void k_apply_rinv(double2* __restrict__ B, int
 // ---------------------------------------------------------------------------
 // restrict / prolong
 // ---------------------------------------------------------------------------
-template <typename R> __device__ __forceinline__ R wsum(R v) {
+// The products below are GEMMs with one long side: per (block, chirality) the
+// basis is a matrix of Nv rows and K = 6 Vb contiguous columns k = (s'col, l),
+// the other operand has up to 16 right-hand sides in a tile.  Both run on the
+// matrix cores (16x16x4) so that each basis and field entry is loaded once, in
+// the lane that multiplies it; they are bound by memory.
+
+// field offset of column k: s'col V + l
+__device__ __forceinline__ size_t col_off(int k, int Vb, size_t V) {
+    int s = 0;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    for (int m = 1; m < 6; ++m) s += k >= m * Vb;
+    return (size_t)s * (V - Vb) + (uint32_t)k;
+}
+template <typename S, typename R> __device__ __forceinline__ void ld1c(const S* p, R& re, R& im) {
+    const cx<R> v = ldc<S, R>(p);
+    re = v.re;
+    im = v.im;
 }
 
-#define RMAXR 16   // right-hand sides per pass
-
-// coarse[r][y][p] = sum_{l, s'col} conj(B[y][p][s'col][l]) fine[r][6 alpha(p) + s'col][y*Vb + l]
-// One workgroup per block, a small GEMM (nc x 6Vb)(6Vb x nrhs) per chirality.
-// lc block sites at a time, the basis rows (padded against LDS bank
-// conflicts) and the field values are staged in LDS with coalesced loads;
-// thread t owns basis vector p = t % nc and right-hand sides
-// r = t / nc + G*q (G = 256 / nc).
-template <typename S, typename R>
-__global__ __launch_bounds__(256) void k_restrict(Geo g, int Nv, const S* __restrict__ B, const S* __restrict__ fine,
-                                                  S* __restrict__ coarse, int nrhs, int lc, int rc) {
-    extern __shared__ char shraw[];
-    const int y = blockIdx.x;
-    const int Vb = g.Vb, nc = 2 * Nv, G = 256 / nc;
-    const int bstride = 6 * lc + 1;
-    cx<R>* Bs = (cx<R>*)shraw;                       // [nc][bstride]
-    cx<R>* Fs = Bs + (size_t)nc * bstride;           // [lc][12][rc]
-    const size_t V = g.V;
-    const int p = threadIdx.x % nc, grp = threadIdx.x / nc;
-    const bool act = grp < G;
-    const int a = p / Nv;
-    const S* Bblk = B + (size_t)y * nc * 6 * Vb;
-    for (int r0 = 0; r0 < nrhs; r0 += rc) {
-        const int nr = nrhs - r0 < rc ? nrhs - r0 : rc;
-        cx<R> acc[RMAXR / 2];
-#pragma unroll
-        for (int q = 0; q < RMAXR / 2; ++q) acc[q] = cmk((R)0, (R)0);
-        for (int l0 = 0; l0 < Vb; l0 += lc) {
-            const int nl = Vb - l0 < lc ? Vb - l0 : lc;
-            __syncthreads();
-            for (int e = threadIdx.x; e < nc * 6 * nl; e += blockDim.x) {
-                const int pp = e / (6 * nl), rem = e - pp * 6 * nl, scl = rem / nl, ll = rem - scl * nl;
-                Bs[pp * bstride + scl * lc + ll] = conj(ldc<S, R>(Bblk + ((size_t)pp * 6 + scl) * Vb + l0 + ll));
-            }
-            for (int e = threadIdx.x; e < nl * 12 * nr; e += blockDim.x) {
-                const int ll = e % nl, t = e / nl, sc = t % 12, r = t / 12;
-                Fs[(ll * 12 + sc) * rc + r] =
-                    ldc<S, R>(fine + ((size_t)(r0 + r) * 12 + sc) * V + (size_t)y * Vb + l0 + ll);
-            }
-            __syncthreads();
-            if (act) {
-                const cx<R>* bp = Bs + p * bstride;
-                for (int ll = 0; ll < nl; ++ll) {
-#pragma unroll
-                    for (int scl = 0; scl < 6; ++scl) {
-                        const cx<R> b = bp[scl * lc + ll];
-                        const cx<R>* f = Fs + (ll * 12 + 6 * a + scl) * rc;
-#pragma unroll
-                        for (int q = 0; q < RMAXR / 2; ++q) {
-                            const int r = grp + G * q;
-                            if (r < nr) cmac(acc[q], b, f[r]);
-                        }
-                    }
-                }
-            }
-        }
-        if (act) {
-#pragma unroll
-            for (int q = 0; q < RMAXR / 2; ++q) {
-                const int r = grp + G * q;
-                if (r < nr) stc<S, R>(coarse + ((size_t)(r0 + r) * g.V1 + y) * nc + p, acc[q]);
-            }
-        }
-    }
-}
-
-// Matrix-core restrictor (v_mfma_*_16x16x4), the same sum as k_restrict.
-// grid (V1, 2 chiralities, ceil(nrhs/16)); 256 threads.  Per (block,
-// chirality) the product is (Nv x 6Vb)(6Vb x 16 rhs): rows p in tiles of 16
-// (at most RMT tiles), the 6Vb columns in chunks of 16 dealt round-robin to
-// the four wavefronts, whose partial tiles are added in LDS in wave order.
-// In an MFMA, lane (lr, lq) takes k = chunk + 4 lq + s for s = 0..3, so its
-// four basis entries and its four field entries are contiguous (needs
-// Vb % 4 == 0 and 16-byte aligned fields, checked by the launcher).
-#define RMT 4
-template <typename R, typename BS = typename VT<R>::c2>
-__global__ __launch_bounds__(256) void k_restrict_mfma(Geo g, int Nv, const BS* __restrict__ B,
-                                                       const typename VT<R>::c2* __restrict__ fine,
-                                                       typename VT<R>::c2* __restrict__ coarse, int nrhs) {
+// coarse[r][y][p] = sum_k conj(B[y][p][k]) fine[r][6 alpha(p) + s'col][y*Vb + l]
+// grid (V1, 2 chiralities, ceil(nrhs/16)).  Rows p in NTR tiles of 16; the K
+// columns in chunks of 16 dealt round-robin to the wavefronts, whose partial
+// tiles are added in LDS in wave order.  Lane (lr, lq) takes four columns of a
+// chunk: VEC (FP32 fields with Vb % 4 == 0 and 16-byte alignment) the
+// contiguous 4 lq + s, else lq + 4 s, where the four lq of a row read one
+// contiguous piece (FP64: 64 bytes).  One chunk in flight: two or four (more
+// loads, more lines of the 16 rows open) cost 5-20 %.  48 x 24^3, 4^4 blocks,
+// 24 vectors, 12 right-hand sides, against chunks of lane-contiguous columns in
+// every precision: FP16 basis 422 -> 382 us, FP32 522 -> 450, FP64 894 -> 855;
+// 18 x 12^3, 3^4 blocks, 10 vectors, 5 right-hand sides in FP64, against the
+// block staged in LDS and multiplied on the vector units: 117 -> 22 us.
+template <typename R, typename BS, int NTR, bool VEC>
+__global__ __launch_bounds__(512) void k_restrict(Geo g, int Nv, const BS* __restrict__ B,
+                                                  const typename VT<R>::c2* __restrict__ fine,
+                                                  typename VT<R>::c2* __restrict__ coarse, int nrhs) {
     typedef typename VT<R>::c2 C2;
     typedef typename Mfma<R>::v4 V4;
     extern __shared__ char shraw[];
-    R* red = (R*)shraw;                       // [4 waves][ntr tiles][re, im][64 lanes][4]
+    R* red = (R*)shraw;                       // [waves][re, im][64 lanes][4]
     const int y = blockIdx.x, a = blockIdx.y, n0 = blockIdx.z * 16;
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int w = threadIdx.x >> 6, nw = blockDim.x >> 6, lane = threadIdx.x & 63;
     const int lr = lane & 15, lq = lane >> 4;
     const int Vb = g.Vb, K = 6 * Vb, nc = 2 * Nv;
-    const int ntr = (Nv + 15) / 16;
     const size_t V = g.V;
-    const int n = n0 + lr;
-    const bool nok = n < nrhs;
-    V4 cr[RMT], ci[RMT];
+    // rows past Nv and right-hand sides past nrhs repeat the last one: their results are not written
+    const BS* Bp[NTR];
 #pragma unroll
-    for (int t = 0; t < RMT; ++t) {
+    for (int t = 0; t < NTR; ++t)
+        Bp[t] = B + ((size_t)(y * 2 + a) * Nv + (t * 16 + lr < Nv ? t * 16 + lr : Nv - 1)) * K;
+    const C2* F = fine + ((size_t)(n0 + lr < nrhs ? n0 + lr : nrhs - 1) * 12 + 6 * a) * V + (size_t)y * Vb;
+    V4 cr[NTR], ci[NTR];
+#pragma unroll
+    for (int t = 0; t < NTR; ++t) {
         cr[t] = V4{0, 0, 0, 0};
         ci[t] = V4{0, 0, 0, 0};
     }
-    const BS* Bya = B + (size_t)(y * 2 + a) * Nv * K;
-    const C2* F = fine + ((size_t)(nok ? n : 0) * 12 + 6 * a) * V + (size_t)y * Vb;
-    const int nchunk = (K + 15) / 16;
-    for (int q = w; q < nchunk; q += 4) {
-        const int kb = q * 16 + 4 * lq;
-        const bool kok = kb < K;
-        R fr[4], fi[4];
-        if (kok && nok) {
-            const int scl = kb / Vb, l = kb - scl * Vb;
-            ld4c(F + (size_t)scl * V + l, fr, fi);
-        } else {
+    const int nfull = K / 16, nchunk = (K + 15) / 16;
+    for (int q = w; q < nchunk; q += nw) {
+        R fr[4], fi[4], br[NTR][4], bi[NTR][4];
+        if (q < nfull) {
+            if constexpr (VEC) {
+                const int k = q * 16 + 4 * lq;
+                ld4c(F + col_off(k, Vb, V), fr, fi);
 #pragma unroll
-            for (int s = 0; s < 4; ++s) fr[s] = fi[s] = (R)0;
-        }
-#pragma unroll
-        for (int t = 0; t < RMT; ++t) {
-            if (t < ntr) {
-                const int p = t * 16 + lr;
-                R br[4], bi[4];
-                if (kok && p < Nv) {
-                    ld4c(Bya + (size_t)p * K + kb, br, bi);
-                } else {
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) br[s] = bi[s] = (R)0;
-                }
+                for (int t = 0; t < NTR; ++t) ld4c(Bp[t] + k, br[t], bi[t]);
+            } else {
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {
-                    // conj(b) f
-                    cr[t] = Mfma<R>::mac(br[s], fr[s], cr[t]);
-                    cr[t] = Mfma<R>::mac(bi[s], fi[s], cr[t]);
-                    ci[t] = Mfma<R>::mac(br[s], fi[s], ci[t]);
-                    ci[t] = Mfma<R>::mac(-bi[s], fr[s], ci[t]);
+                    const int k = q * 16 + lq + 4 * s;
+                    ld1c<C2, R>(F + col_off(k, Vb, V), fr[s], fi[s]);
+#pragma unroll
+                    for (int t = 0; t < NTR; ++t) ld1c<BS, R>(Bp[t] + k, br[t][s], bi[t][s]);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int k = q * 16 + (VEC ? 4 * lq + s : lq + 4 * s);
+                fr[s] = fi[s] = (R)0;
+                if (k < K) ld1c<C2, R>(F + col_off(k, Vb, V), fr[s], fi[s]);
+#pragma unroll
+                for (int t = 0; t < NTR; ++t) {
+                    br[t][s] = bi[t][s] = (R)0;
+                    if (k < K) ld1c<BS, R>(Bp[t] + k, br[t][s], bi[t][s]);
                 }
             }
         }
-    }
 #pragma unroll
-    for (int t = 0; t < RMT; ++t) {
-        if (t < ntr) {
-            R* o = red + (((size_t)w * ntr + t) * 2) * 256 + lane * 4;
+        for (int t = 0; t < NTR; ++t)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                o[j] = cr[t][j];
-                o[256 + j] = ci[t][j];
+            for (int s = 0; s < 4; ++s) {
+                // conj(b) f
+                cr[t] = Mfma<R>::mac(br[t][s], fr[s], cr[t]);
+                cr[t] = Mfma<R>::mac(bi[t][s], fi[s], cr[t]);
+                ci[t] = Mfma<R>::mac(br[t][s], fi[s], ci[t]);
+                ci[t] = Mfma<R>::mac(-bi[t][s], fr[s], ci[t]);
             }
+    }
+    // thread -> (row p, rhs n) of a tile, p fastest
+    const int pl = threadIdx.x & 15, nl = (threadIdx.x >> 4) & 15;
+    const int src = (sizeof(R) == 8 ? ((pl & 3) * 16 + nl) * 4 + (pl >> 2) : ((pl >> 2) * 16 + nl) * 4 + (pl & 3));
+#pragma unroll
+    for (int t = 0; t < NTR; ++t) {
+        R* o = red + (size_t)w * 512 + lane * 4;
+        if (t) __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            o[j] = cr[t][j];
+            o[256 + j] = ci[t][j];
         }
-    }
-    __syncthreads();
-    // thread -> (lane l, register j): output row 16 t + row(l / 16, j), rhs n0 + l % 16
-    const int l = threadIdx.x & 63, j = threadIdx.x >> 6;
-    const int nn = n0 + (l & 15);
-    for (int t = 0; t < ntr; ++t) {
-        const int p = t * 16 + Mfma<R>::row(l >> 4, j);
-        if (p < Nv && nn < nrhs) {
+        __syncthreads();
+        if (threadIdx.x < 256 && t * 16 + pl < Nv && n0 + nl < nrhs) {
             R sr = 0, si = 0;
-#pragma unroll
-            for (int ww = 0; ww < 4; ++ww) {
-                const R* o = red + (((size_t)ww * ntr + t) * 2) * 256 + l * 4 + j;
-                sr += o[0];
-                si += o[256];
+            for (int ww = 0; ww < nw; ++ww) {
+                sr += red[ww * 512 + src];
+                si += red[ww * 512 + 256 + src];
             }
-            coarse[((size_t)nn * g.V1 + y) * nc + a * Nv + p] = C2{sr, si};
+            coarse[((size_t)(n0 + nl) * g.V1 + y) * nc + a * Nv + t * 16 + pl] = C2{sr, si};
         }
     }
 }
 
-// fine[r][6a + s'col][i] = sum_c B[y][a][c][s'col][l] coarse[r][y][a*Nv + c]
-// One thread per fine site; the coarse vectors of the workgroup's blocks are
-// staged in LDS (RMAXR right-hand sides per pass).
-template <typename S, typename R, typename BS = S>
-__global__ __launch_bounds__(256) void k_prolong(Geo g, int Nv, const BS* __restrict__ B, const S* __restrict__ coarse,
-                                                 S* __restrict__ fine, int nrhs, int nbw, int rc) {
-    extern __shared__ char shraw[];
-    cx<R>* CS = (cx<R>*)shraw;    // [nbw][nc][rc], rc <= RMAXR right-hand sides per pass
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const int Vb = g.Vb, nc = 2 * Nv;
-    const int yfirst = (blockIdx.x * blockDim.x) / Vb;
-    const int y = i / Vb, l = i - y * Vb;
+// fine[r][6a + s'col][y*Vb + l] = sum_c B[y][a][c][k] coarse[r][y][a*Nv + c]
+// grid (V1, 2 chiralities, groups of right-hand sides x ns).  The coarse
+// vectors stay in registers (NS steps of four basis vectors; zero past Nv);
+// each wavefront walks tiles of 16 W columns, lane lr the W columns from
+// W lr on, so that a row of 16 lanes reads and writes 16 W contiguous entries.
+// W = 4 (FP32 fields) needs Vb % 4 == 0 and 16-byte alignment.  At the rate of
+// a copy: sizes as above, against one thread a site on the vector units, FP16
+// basis 461 -> 318 us (4.6 TB/s), FP32 531 -> 520, FP64 1031 -> 860; 3^4
+// blocks, FP64: 38 -> 18 us; 8^4, 4^4 blocks, 8 vectors, one right-hand side:
+// 15 -> 5 us (ns workgroups a block).
+template <typename R, typename BS, int NS, int W>
+__global__ __launch_bounds__(256) void k_prolong(Geo g, int Nv, const BS* __restrict__ B,
+                                                 const typename VT<R>::c2* __restrict__ coarse,
+                                                 typename VT<R>::c2* __restrict__ fine, int nrhs, int ns) {
+    typedef typename VT<R>::c2 C2;
+    typedef typename Mfma<R>::v4 V4;
+    const int y = blockIdx.x, a = blockIdx.y, ng = blockIdx.z / ns, n0 = ng * 16;
+    const int w = (threadIdx.x >> 6) + 4 * (blockIdx.z - ng * ns), lane = threadIdx.x & 63;
+    const int lr = lane & 15, lq = lane >> 4;
+    const int Vb = g.Vb, K = 6 * Vb, nc = 2 * Nv;
     const size_t V = g.V;
-    for (int r0 = 0; r0 < nrhs; r0 += rc) {
-        const int nr = nrhs - r0 < rc ? nrhs - r0 : rc;
-        __syncthreads();
-        for (int e = threadIdx.x; e < nbw * nc * nr; e += blockDim.x) {
-            const int r = e % nr, t = e / nr, j = t % nc, yb = t / nc;
-            const int yy = yfirst + yb;
-            CS[(yb * nc + j) * rc + r] =
-                yy < g.V1 ? ldc<S, R>(coarse + ((size_t)(r0 + r) * g.V1 + yy) * nc + j) : cmk((R)0, (R)0);
+    R xr[NS], xi[NS];
+    const C2* X = coarse + ((size_t)(n0 + lr < nrhs ? n0 + lr : nrhs - 1) * g.V1 + y) * nc + a * Nv;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const int c = 4 * s + lq;
+        const C2 v = X[c < Nv ? c : Nv - 1];
+        xr[s] = c < Nv ? v.x : (R)0;
+        xi[s] = c < Nv ? v.y : (R)0;
+    }
+    const BS* Bya = B + (size_t)(y * 2 + a) * Nv * K;
+    C2* F = fine + ((size_t)n0 * 12 + 6 * a) * V + (size_t)y * Vb;
+    const int nt = (K + 16 * W - 1) / (16 * W);
+    for (int q = w; q < nt; q += 4 * ns) {
+        const int k = (q * 16 + lr) * W;
+        const bool kok = k < K;
+        const BS* bp = Bya + (kok ? k : 0);
+        V4 dr[W], di[W];
+#pragma unroll
+        for (int u = 0; u < W; ++u) {
+            dr[u] = V4{0, 0, 0, 0};
+            di[u] = V4{0, 0, 0, 0};
         }
-        __syncthreads();
-        if (i < g.V) {
-            // three spin-colour planes per pass: each coarse value read from LDS
-            // serves three basis entries
-            const cx<R>* cy = CS + (size_t)(y - yfirst) * nc * rc;
-            for (int a = 0; a < 2; ++a) {
-                for (int s0 = 0; s0 < 6; s0 += 3) {
-                    cx<R> acc[3][RMAXR];
+        R br[NS][W], bi[NS][W];
 #pragma unroll
-                    for (int u = 0; u < 3; ++u)
+        for (int s = 0; s < NS; ++s) {
+            const int c = 4 * s + lq;
+            const BS* p = bp + (size_t)(c < Nv ? c : Nv - 1) * K;
+            if constexpr (W == 4) ld4c(p, br[s], bi[s]);
+            else ld1c<BS, R>(p, br[s][0], bi[s][0]);
+        }
 #pragma unroll
-                        for (int q = 0; q < RMAXR; ++q) acc[u][q] = cmk((R)0, (R)0);
-                    for (int c = 0; c < Nv; ++c) {
-                        const BS* bp = B + (((size_t)y * nc + a * Nv + c) * 6 + s0) * Vb + l;
-                        cx<R> b[3];
+        for (int s = 0; s < NS; ++s)
 #pragma unroll
-                        for (int u = 0; u < 3; ++u) b[u] = ldc<BS, R>(bp + (size_t)u * Vb);
-                        const cx<R>* cv = cy + (a * Nv + c) * rc;
+            for (int u = 0; u < W; ++u) {
+                dr[u] = Mfma<R>::mac(xr[s], br[s][u], dr[u]);
+                dr[u] = Mfma<R>::mac(-xi[s], bi[s][u], dr[u]);
+                di[u] = Mfma<R>::mac(xi[s], br[s][u], di[u]);
+                di[u] = Mfma<R>::mac(xr[s], bi[s][u], di[u]);
+            }
+        if (kok) {
+            C2* f = F + col_off(k, Vb, V);
 #pragma unroll
-                        for (int q = 0; q < RMAXR; ++q)
-                            if (q < nr) {
-                                const cx<R> x = cv[q];
-#pragma unroll
-                                for (int u = 0; u < 3; ++u) cmac(acc[u][q], b[u], x);
-                            }
+            for (int j = 0; j < 4; ++j) {
+                const int n = Mfma<R>::row(lq, j);
+                if (n0 + n < nrhs) {
+                    C2* o = f + (size_t)n * 12 * V;
+                    if constexpr (W == 4) {
+                        *(float4*)o = make_float4(dr[0][j], di[0][j], dr[1][j], di[1][j]);
+                        *(float4*)(o + 2) = make_float4(dr[2][j], di[2][j], dr[3][j], di[3][j]);
+                    } else {
+                        o[0] = C2{dr[0][j], di[0][j]};
                     }
-#pragma unroll
-                    for (int u = 0; u < 3; ++u)
-#pragma unroll
-                        for (int q = 0; q < RMAXR; ++q)
-                            if (q < nr)
-                                stc<S, R>(fine + ((size_t)(r0 + q) * 12 + 6 * a + s0 + u) * V + i, acc[u][q]);
                 }
             }
         }
     }
+}
+
+// FP32 fields: four columns a lane at once
+static bool cols4(const Geo& g, const void* fine) { return g.Vb % 4 == 0 && (uintptr_t)fine % 16 == 0; }
+
+template <typename R, typename BS, bool VEC>
+static int restrict_launch(mglma_ctx* c, const BS* B, const void* fine, void* coarse, int nrhs) {
+    typedef typename VT<R>::c2 C2;
+    const Geo& g = c->geo;
+    const dim3 grid(g.V1, 2, (nrhs + 15) / 16);
+    // few blocks: eight wavefronts share a block's columns (16 blocks, one right-hand side: 18 -> 12 us; on
+    // 2592 blocks eight cost 430 instead of 380 us)
+    const int nw = (size_t)g.V1 * 2 * grid.z < 512 ? 8 : 4;
+    const size_t shb = (size_t)nw * 512 * sizeof(R);
+    switch ((c->Nv + 15) / 16) {
+#define CASE(N)                                                                                                   \
+    case N:                                                                                                       \
+        hipLaunchKernelGGL((k_restrict<R, BS, N, VEC>), grid, dim3(64 * nw), shb, c->stream, g, c->Nv, B,         \
+                           (const C2*)fine, (C2*)coarse, nrhs);                                                   \
+        break;
+        CASE(1) CASE(2) CASE(3) CASE(4)
+#undef CASE
+        default: return MGLMA_ERR_SHAPE;
+    }
+    HIP_TRY(hipGetLastError());
+    return MGLMA_OK;
 }
 
 int mg_restrict(mglma_ctx* c, int prec, const void* fine, void* coarse, int nrhs) {
     if (nrhs <= 0) return MGLMA_OK;
-    const Geo& g = c->geo;
-    const int nc = c->nc;
+    const bool v = cols4(c->geo, fine);
     if (prec == MGLMA_F16) {
-        // FP32 fields, FP16 basis (matrix-core restrictor), else the FP32 basis
-        if (g.Vb % 4 == 0 && c->Nv <= 16 * RMT && (uintptr_t)fine % 16 == 0) {
-            dim3 grid(g.V1, 2, (nrhs + 15) / 16);
-            const size_t shb = (size_t)4 * ((c->Nv + 15) / 16) * 2 * 256 * 4;
-            hipLaunchKernelGGL((k_restrict_mfma<float, __half2>), grid, dim3(256), shb, c->stream, g, c->Nv, c->B16,
-                               (const float2*)fine, (float2*)coarse, nrhs);
-            HIP_TRY(hipGetLastError());
-            return MGLMA_OK;
-        }
+        // FP32 fields, FP16 basis (four columns at once), else the FP32 basis
+        if (v) return restrict_launch<float, __half2, true>(c, c->B16, fine, coarse, nrhs);
         prec = MGLMA_F32;
     }
-    if (prec != MGLMA_F64 && prec != MGLMA_F32) return MGLMA_ERR_ARG;
-    if (prec == MGLMA_F32) MG_TRY(mg_need_b32(c));
-    const size_t cb = prec == MGLMA_F64 ? 16 : 8;
-    if (g.Vb % 4 == 0 && c->Nv <= 16 * RMT && (uintptr_t)fine % 16 == 0) {
-        dim3 grid(g.V1, 2, (nrhs + 15) / 16);
-        const size_t shb = (size_t)4 * ((c->Nv + 15) / 16) * 2 * 256 * (cb / 2);
-        if (prec == MGLMA_F64)
-            hipLaunchKernelGGL(k_restrict_mfma<double>, grid, dim3(256), shb, c->stream, g, c->Nv, c->B64,
-                               (const double2*)fine, (double2*)coarse, nrhs);
-        else
-            hipLaunchKernelGGL(k_restrict_mfma<float>, grid, dim3(256), shb, c->stream, g, c->Nv, c->B32,
-                               (const float2*)fine, (float2*)coarse, nrhs);
-        HIP_TRY(hipGetLastError());
-        return MGLMA_OK;
-    }
-    // general block shapes: LDS-staged VALU kernel.
-    // LDS budget: 32 KiB of basis rows, 24 KiB of field values
-    int lc = (int)(32768 / (6 * nc * cb));
-    if (lc > 16) lc = 16;
-    if (lc > g.Vb) lc = g.Vb;
-    if (lc < 1) lc = 1;
-    int rc = (int)(24576 / ((size_t)lc * 12 * cb));
-    if (rc > RMAXR) rc = RMAXR;
-    if (rc < 1) return MGLMA_ERR_SHAPE;
-    const size_t shb = ((size_t)nc * (6 * lc + 1) + (size_t)lc * 12 * rc) * cb;
-    if (prec == MGLMA_F64)
-        hipLaunchKernelGGL((k_restrict<double2, double>), dim3(g.V1), dim3(256), shb, c->stream, g, c->Nv, c->B64,
-                           (const double2*)fine, (double2*)coarse, nrhs, lc, rc);
-    else
-        hipLaunchKernelGGL((k_restrict<float2, float>), dim3(g.V1), dim3(256), shb, c->stream, g, c->Nv, c->B32,
-                           (const float2*)fine, (float2*)coarse, nrhs, lc, rc);
+    if (prec == MGLMA_F64) return restrict_launch<double, double2, false>(c, c->B64, fine, coarse, nrhs);
+    if (prec != MGLMA_F32) return MGLMA_ERR_ARG;
+    MG_TRY(mg_need_b32(c));
+    if (v) return restrict_launch<float, float2, true>(c, c->B32, fine, coarse, nrhs);
+    return restrict_launch<float, float2, false>(c, c->B32, fine, coarse, nrhs);
+}
+
+template <typename R, typename BS, int W>
+static int prolong_launch(mglma_ctx* c, const BS* B, const void* coarse, void* fine, int nrhs) {
+    typedef typename VT<R>::c2 C2;
+    const Geo& g = c->geo;
+    const int ng = (nrhs + 15) / 16, nt = (6 * g.Vb + 16 * W - 1) / (16 * W);
+    // few blocks: ns workgroups share a block's columns, at least four tiles (one a wavefront) each
+    long long ns = (1024 + 2LL * g.V1 * ng - 1) / (2LL * g.V1 * ng);
+    if (ns > (nt + 3) / 4) ns = (nt + 3) / 4;
+    const dim3 grid(g.V1, 2, (unsigned)(ng * ns));
+#define LAUNCH(NS)                                                                                              \
+    hipLaunchKernelGGL((k_prolong<R, BS, NS, W>), grid, dim3(256), 0, c->stream, g, c->Nv, B, (const C2*)coarse, \
+                       (C2*)fine, nrhs, (int)ns)
+    if (c->Nv <= 12) LAUNCH(3);
+    else if (c->Nv <= 20) LAUNCH(5);
+    else if (c->Nv <= 24) LAUNCH(6);
+    else if (c->Nv <= 32) LAUNCH(8);
+    else LAUNCH(16);
+#undef LAUNCH
     HIP_TRY(hipGetLastError());
     return MGLMA_OK;
 }
@@ -449,31 +433,21 @@ int mg_restrict(mglma_ctx* c, int prec, const void* fine, void* coarse, int nrhs
 int mg_prolong(mglma_ctx* c, int prec, const void* coarse, void* fine, int nrhs) {
     if (nrhs <= 0) return MGLMA_OK;
     const Geo& g = c->geo;
-    dim3 grid((g.V + 255) / 256);
-    const int nbw = 255 / g.Vb + 2;   // blocks a 256-site workgroup can touch
+    // blocks of few sites with many vectors are refused
     const size_t cb = prec == MGLMA_F64 ? sizeof(cx<double>) : sizeof(cx<float>);
-    int rc = (int)((48 * 1024) / ((size_t)nbw * c->nc * cb));
-    if (rc > RMAXR) rc = RMAXR;
-    if (rc < 1) return MGLMA_ERR_SHAPE;
-    const size_t shb = (size_t)nbw * c->nc * rc * cb;
+    if ((size_t)(255 / g.Vb + 2) * c->nc * cb > 48 * 1024) return MGLMA_ERR_SHAPE;
+    const bool v = cols4(g, fine);
     switch (prec) {
-        case MGLMA_F64:
-            hipLaunchKernelGGL((k_prolong<double2, double>), grid, dim3(256), shb, c->stream, g, c->Nv, c->B64,
-                               (const double2*)coarse, (double2*)fine, nrhs, nbw, rc);
-            break;
+        case MGLMA_F64: return prolong_launch<double, double2, 1>(c, c->B64, coarse, fine, nrhs);
         case MGLMA_F32:
             MG_TRY(mg_need_b32(c));
-            hipLaunchKernelGGL((k_prolong<float2, float>), grid, dim3(256), shb, c->stream, g, c->Nv, c->B32,
-                               (const float2*)coarse, (float2*)fine, nrhs, nbw, rc);
-            break;
+            if (v) return prolong_launch<float, float2, 4>(c, c->B32, coarse, fine, nrhs);
+            return prolong_launch<float, float2, 1>(c, c->B32, coarse, fine, nrhs);
         case MGLMA_F16:   // FP32 fields, FP16 basis
-            hipLaunchKernelGGL((k_prolong<float2, float, __half2>), grid, dim3(256), shb, c->stream, g, c->Nv, c->B16,
-                               (const float2*)coarse, (float2*)fine, nrhs, nbw, rc);
-            break;
+            if (v) return prolong_launch<float, __half2, 4>(c, c->B16, coarse, fine, nrhs);
+            return prolong_launch<float, __half2, 1>(c, c->B16, coarse, fine, nrhs);
         default: return MGLMA_ERR_ARG;
     }
-    HIP_TRY(hipGetLastError());
-    return MGLMA_OK;
 }
 
 extern "C" int mglma_restrict(mglma_ctx* c, int prec, const void* fine, void* coarse, int nrhs) {

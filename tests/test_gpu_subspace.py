@@ -82,6 +82,33 @@ def test_restrict_prolong_parity(pair, prec, tol):
     assert e_p < tol
 
 
+# block, vectors, right-hand sides: every number of 16-row tiles and of four-vector steps, columns in
+# and out of fours and of whole chunks, one block (several workgroups or wavefronts for it), and
+# fields off the 16-byte alignment that four columns at once need
+@pytest.mark.parametrize("b,Nv,n,shift", [((2, 2, 2, 2), 13, 1, 0), ((2, 2, 2, 2), 24, 8, 1), ((3, 3, 3, 3), 33, 17, 0),
+                                          ((3, 2, 1, 1), 20, 5, 0), ((4, 4, 4, 4), 64, 16, 0), ((4, 4, 4, 4), 1, 2, 1)])
+@pytest.mark.parametrize("prec,tol", [(0, 1e-12), (1, 2e-6), (2, 1e-3)])
+def test_transfer_shapes(b, Nv, n, shift, prec, tol):
+    import torch
+    L = b if b[0] == 4 else tuple(2 * m for m in b)
+    pair = Pair(L, b, Nv, oracle_galerkin=False)
+    fp = 1 if prec == 2 else prec
+    cdt = torch.float64 if prec == 0 else torch.float32
+    psi = synth.gaussian_fields(n, L, 79)
+    src = pair.fine_dev(psi, fp)
+    buf = torch.zeros(src.numel() + 2, dtype=src.dtype, device="cuda")
+    x = buf[2 * shift:2 * shift + src.numel()].view(src.shape)
+    x.copy_(src)
+    c = torch.empty((n, pair.bl.V1, 2 * Nv, 2), dtype=cdt, device="cuda")
+    pair.ctx.restrict(x, c, prec)
+    assert relerr(from_dev(c), pair.B.restrict(pair.lat(psi))) < tol
+    cv = synth.gaussian_coarse(n, pair.bl.V1, 2 * Nv, 80)
+    pair.ctx.prolong(to_dev(cv).to(cdt), x, prec)
+    torch.cuda.synchronize()
+    assert relerr(pair.fine_host(x.clone(), fp), pair.canon(pair.B.prolong(cv))) < tol
+    assert float(buf[:2 * shift].abs().sum()) == 0 and float(buf[2 * shift + src.numel():].abs().sum()) == 0
+
+
 @pytest.mark.parametrize("prec,tol", [(0, 1e-12), (1, 2e-6), (3, 2e-2)])
 @pytest.mark.parametrize("gamma5", [0, 1])
 def test_coarse_apply_parity(pair, prec, tol, gamma5):
