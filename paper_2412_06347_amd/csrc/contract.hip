@@ -156,27 +156,29 @@ __global__ __launch_bounds__(256) void k_fine_slice_part(Geo g, int nchunk, int 
 // Coarse pieces on the FP64 matrix cores (v_mfma_f64_16x16x4): with Gb the
 // stored alpha = 0 x alpha = 1 block of (gamma5 gamma_k)_1(y, t),
 //   u^+ Gamma v = u_0^+ Gb v_1 - conj(v_0^+ Gb u_1),
-// and T = Gb [v_1 of 16 columns] is a GEMM whose columns are 16 / (4 NCS)
+// and S = [u_0 of 16 columns]^+ Gb is a GEMM whose rows are 16 / (4 NCS)
 // (piece, source) groups.  One workgroup per (block row y0, chunk of its
-// coarse sites, column tile), the tiles of a chunk back to back on one XCD;
+// coarse sites, row tile), the tiles of a chunk back to back on one XCD;
 // wavefront w takes the block time slice w % b0 (every ns-th site of the
-// chunk when b0 <= 2), so Gb is read once per tile in 64-byte runs and each
-// lane then weights its own rows of T with conj(u_0).  MFMA lane (lr, lq)
-// supplies A[row lr][4 s + lq], B[4 s + lq][col lr]; Nv is walked in steps of
-// four, the tail masked.  SAME (u = v): the second product is minus the
-// conjugate of the first one with the columns exchanged, so the sum is twice
-// the real part of the first.
+// chunk when b0 <= 2).  MFMA lane (lr, lq) supplies A[row lr][4 s + lq] and
+// B[4 s + lq][col lr], so a step of NS reads four rows of Gb whole; the lane
+// then weights its own columns of S with v_1.  SAME (u = v): the second
+// product is minus the conjugate of the first one with the columns exchanged,
+// so the sum is twice the real part of the first.
 //
 // Bound: HBM, 3 b0 Nv^2 complex of Gb per coarse site (287 MB on 48 x 24^3,
-// Nv = 24).  Two pieces of 12 columns there: 1.14 ms with the Nv x Nv products
-// spread over lanes and summed by shuffles per term, 0.51 ms here.
-template <int NCS, bool SAME, int RT>
+// Nv = 24), and about as long in the matrix cores for two row tiles.  NS >= Nv
+// / 4 steps are unrolled, so that the loads of a whole Gb are in flight.  Two
+// pieces of 12 columns there: 1.14 ms with the Nv x Nv products spread over
+// lanes and summed by shuffles per term, 0.51 ms with T = Gb v_1 (16 rows of Gb
+// in 64-byte runs, two steps in flight), 0.18 ms here.
+template <int NCS, bool SAME, int NS>
 __global__ __launch_bounds__(256) void k_coarse_slice_part(Geo g, int Nv, int nchunk, int nsrc, int npn, int pair0,
                                                            const double2* __restrict__ G1, PairSet P, double scale,
                                                            double2* __restrict__ part) {
     typedef Mfma<double>::v4 V4;
-    constexpr int NCOL = 4 * NCS, GPT = 16 / NCOL;
-    __shared__ double2 red[4][16];
+    constexpr int NCOL = 4 * NCS, GPT = 16 / NCOL, RT = (NS + 3) / 4, GS = NS <= 8 ? NS : 4;
+    __shared__ double2 red[4][GPT];
     int item, tile;
     if (!site_tile(g.L1[0] * nchunk, (npn + GPT - 1) / GPT, &item, &tile)) return;
     const int y0 = item / nchunk, ch = item - y0 * nchunk;
@@ -184,27 +186,48 @@ __global__ __launch_bounds__(256) void k_coarse_slice_part(Geo g, int Nv, int nc
     const int ys0 = (int)((long)rowsz * ch / nchunk), ys1 = (int)((long)rowsz * (ch + 1) / nchunk);
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4;
     const int nc = 2 * Nv;
-    const size_t V1 = g.V1, nn = (size_t)Nv * Nv;
+    const size_t cs = (size_t)g.V1 * nc, nn = (size_t)Nv * Nv;
     const int nsub = b0 >= 4 ? 1 : 4 / b0;       // wavefronts per time slice
     const int sub = b0 >= 4 ? 0 : w / b0;
-    // column lr of the tile: group (piece, source) tile * GPT + lr / NCOL, source column a
-    const int pn = tile * GPT + lr / NCOL, a = lr % NCOL;
-    const bool con = lr < GPT * NCOL && pn < npn;
-    const int p = con ? pn / nsrc : 0, n = con ? pn - p * nsrc : 0;
-    const int sa = a / NCS, sc = a - sa * NCS;
-    const double2* vi = P.pi[p] + (size_t)n * NCOL * V1 * nc;
-    const double2* vj = P.pj[p] + (size_t)n * NCOL * V1 * nc;
-    const double2* va = vi + (size_t)a * V1 * nc;
+    // row lr of the tile: group (piece, source) tile * GPT + lr / NCOL, source column lr % NCOL
+    const int pl = tile * GPT + lr / NCOL;
+    const bool con = lr < GPT * NCOL && pl < npn;
+    const size_t ao = con ? (size_t)(pl % nsrc * NCOL + lr % NCOL) * cs : 0;
+    const double2* uj = P.pj[con ? pl / nsrc : 0] + ao;
+    const double2* vi = P.pi[con ? pl / nsrc : 0] + ao;
+    // result register r: row lq + 4 r, of group r / NCS and source column lq + 4 (r % NCS)
+    const double2 *wi_[GPT], *wj_[GPT];
+#pragma unroll
+    for (int q = 0; q < GPT; ++q) {
+        const int pn = tile * GPT + q < npn ? tile * GPT + q : npn - 1;
+        wi_[q] = P.pi[pn / nsrc] + (size_t)(pn % nsrc) * NCOL * cs + Nv;
+        wj_[q] = P.pj[pn / nsrc] + (size_t)(pn % nsrc) * NCOL * cs + Nv;
+    }
     for (int t0 = 0; t0 < b0; t0 += 4) {
         const int t = b0 >= 4 ? t0 + w : w % b0;
-        double re = 0.0, im = 0.0;
+        double re[GPT], im[GPT];
+#pragma unroll
+        for (int q = 0; q < GPT; ++q) re[q] = im[q] = 0.0;
         if (t < b0 && sub < nsub) {
             for (int ys = ys0 + sub; ys < ys1; ys += nsub) {
                 const int y = y0 * rowsz + ys;
-                const double2* v1 = va + (size_t)y * nc + Nv;
+                double ar[NS], ai[NS], br[SAME ? 1 : NS], bi[SAME ? 1 : NS];
+#pragma unroll
+                for (int s = 0; s < NS; ++s) {
+                    const int c = 4 * s + lq;
+                    const bool cok = con && c < Nv;
+                    const uint32_t o = (uint32_t)y * (uint32_t)nc + (cok ? c : 0);
+                    const double2 u = uj[o];
+                    ar[s] = cok ? u.x : 0.0;
+                    ai[s] = cok ? u.y : 0.0;
+                    if (!SAME) {
+                        const double2 v = vi[o];
+                        br[s] = cok ? v.x : 0.0;
+                        bi[s] = cok ? v.y : 0.0;
+                    }
+                }
+#pragma unroll 1
                 for (int k = 1; k <= 3; ++k) {
-                    const int sb = k < 3 ? 3 - sa : sa ^ 2;
-                    const size_t boff = ((size_t)(sb * NCS + sc) * V1 + y) * nc;
                     const double2* Gb = G1 + (((size_t)y * b0 + t) * 3 + (k - 1)) * nn;
                     V4 cr[RT], ci[RT], dr[SAME ? 1 : RT], di[SAME ? 1 : RT];
 #pragma unroll
@@ -212,71 +235,89 @@ __global__ __launch_bounds__(256) void k_coarse_slice_part(Geo g, int Nv, int nc
                         cr[rt] = ci[rt] = V4{0, 0, 0, 0};
                         if (!SAME) dr[rt] = di[rt] = V4{0, 0, 0, 0};
                     }
-#pragma unroll 2
-                    for (int d0 = 0; d0 < Nv; d0 += 4) {
-                        const int d = d0 + lq;
-                        const bool dok = d < Nv;
-                        const double2 z = make_double2(0.0, 0.0);
-                        const double2 b = (dok && con) ? v1[d] : z;
-                        const double2 b2 = (!SAME && dok && con) ? vj[boff + Nv + d] : z;
 #pragma unroll
-                        for (int rt = 0; rt < RT; ++rt) {
-                            const int c = 16 * rt + lr;
-                            const double2 ga = (dok && c < Nv) ? Gb[(size_t)c * Nv + d] : z;
-                            cr[rt] = Mfma<double>::mac(ga.x, b.x, cr[rt]);
-                            cr[rt] = Mfma<double>::mac(-ga.y, b.y, cr[rt]);
-                            ci[rt] = Mfma<double>::mac(ga.x, b.y, ci[rt]);
-                            ci[rt] = Mfma<double>::mac(ga.y, b.x, ci[rt]);
-                            if (!SAME) {
-                                dr[rt] = Mfma<double>::mac(ga.x, b2.x, dr[rt]);
-                                dr[rt] = Mfma<double>::mac(-ga.y, b2.y, dr[rt]);
-                                di[rt] = Mfma<double>::mac(ga.x, b2.y, di[rt]);
-                                di[rt] = Mfma<double>::mac(ga.y, b2.x, di[rt]);
+                    for (int s0 = 0; s0 < NS; s0 += GS) {
+                        double2 gv[GS][RT];
+#pragma unroll
+                        for (int s = 0; s < GS; ++s)
+#pragma unroll
+                            for (int rt = 0; rt < RT; ++rt) {
+                                const int c = 4 * (s0 + s) + lq, d = 16 * rt + lr;
+                                gv[s][rt] = Gb[(c < Nv ? c : Nv - 1) * Nv + (d < Nv ? d : Nv - 1)];
                             }
-                        }
-                    }
-                    // x = u_0^+ T (- conj(v_0^+ T_u)) over this lane's rows, times G_k[sa][sb]
-                    cx<double> x = cmk(0.0, 0.0), x2 = cmk(0.0, 0.0);
-                    if (con) {
 #pragma unroll
-                        for (int rt = 0; rt < RT; ++rt)
+                        for (int s = 0; s < GS; ++s)
 #pragma unroll
-                            for (int r = 0; r < 4; ++r) {
-                                const int c = 16 * rt + Mfma<double>::row(lq, r);
-                                if (c < Nv) {
-                                    cjmac(x, ldc<double2, double>(vj + boff + c), cmk(cr[rt][r], ci[rt][r]));
-                                    if (!SAME)
-                                        cjmac(x2, ldc<double2, double>(va + (size_t)y * nc + c),
-                                              cmk(dr[rt][r], di[rt][r]));
+                            for (int rt = 0; rt < RT; ++rt) {
+                                const double2 b = gv[s][rt];
+                                cr[rt] = Mfma<double>::mac(ar[s0 + s], b.x, cr[rt]);
+                                cr[rt] = Mfma<double>::mac(ai[s0 + s], b.y, cr[rt]);
+                                ci[rt] = Mfma<double>::mac(ar[s0 + s], b.y, ci[rt]);
+                                ci[rt] = Mfma<double>::mac(-ai[s0 + s], b.x, ci[rt]);
+                                if (!SAME) {
+                                    dr[rt] = Mfma<double>::mac(br[s0 + s], b.x, dr[rt]);
+                                    dr[rt] = Mfma<double>::mac(bi[s0 + s], b.y, dr[rt]);
+                                    di[rt] = Mfma<double>::mac(br[s0 + s], b.y, di[rt]);
+                                    di[rt] = Mfma<double>::mac(-bi[s0 + s], b.x, di[rt]);
                                 }
                             }
+                        if (GS < NS) __builtin_amdgcn_sched_barrier(0);   // bounded register use
                     }
-                    int tc;
-                    double wr, wi;
-                    gk_row(k, sa, &tc, &wr, &wi);
-                    const cx<double> f = SAME ? cmk(2.0 * (wr * x.re - wi * x.im), 0.0) : cmk(wr, wi) * (x - conj(x2));
-                    re += f.re;
-                    im += SAME ? 0.0 * f.re : f.im;
+                    // row of spin s, partner of spin sp: S v_1 (partner's v for u_0, partner's u for v_0)
+#pragma unroll
+                    for (int r = 0; r < GPT * NCS; ++r) {
+                        const int q = r / NCS, col = lq + 4 * (r % NCS), sp = col / NCS, sc = col - sp * NCS;
+                        const int pt = gk_col(k, sp);
+                        const uint32_t o = (uint32_t)y * (uint32_t)nc;
+                        const double2* pv = wi_[q] + (size_t)(pt * NCS + sc) * cs + o;
+                        const double2* pu = wj_[q] + (size_t)(pt * NCS + sc) * cs + o;
+                        cx<double> x = cmk(0.0, 0.0), x2 = cmk(0.0, 0.0);
+#pragma unroll
+                        for (int rt = 0; rt < RT; ++rt) {
+                            const int d = 16 * rt + lr;
+                            if (d < Nv) {
+                                cmac(x, cmk(cr[rt][r], ci[rt][r]), ldc<double2, double>(pv + d));
+                                if (!SAME) cmac(x2, cmk(dr[rt][r], di[rt][r]), ldc<double2, double>(pu + d));
+                            }
+                        }
+                        int tc;
+                        double wr, wi;
+                        gk_row(k, pt, &tc, &wr, &wi);    // u_0 in row sp: G_k[pt][sp]
+                        if (SAME) {
+                            re[q] += 2.0 * (wr * x.re - wi * x.im);
+                        } else {
+                            cx<double> f = cmk(wr, wi) * x;
+                            gk_row(k, sp, &tc, &wr, &wi);   // v_0 in row sp: G_k[sp][pt]
+                            f = f - cmk(wr, wi) * conj(x2);
+                            re[q] += f.re;
+                            im[q] += f.im;
+                        }
+                    }
                 }
             }
         }
-        // rows (the four lanes of a column), then the columns of a group and
-        // the wavefronts of a time slice, all in a fixed order
-        re += __shfl_xor(re, 16, 64); im += __shfl_xor(im, 16, 64);
-        re += __shfl_xor(re, 32, 64); im += __shfl_xor(im, 32, 64);
-        if (lq == 0) red[w][lr] = make_double2(re, im);
+        // the wavefront's lanes, then the wavefronts of a time slice, all in a fixed order
+#pragma unroll
+        for (int q = 0; q < GPT; ++q) {
+            if (SAME) im[q] = 0.0 * re[q];
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                re[q] += __shfl_xor(re[q], o, 64);
+                im[q] += __shfl_xor(im[q], o, 64);
+            }
+            if (lane == 0) red[w][q] = make_double2(re[q], im[q]);
+        }
         __syncthreads();
         const int nt = b0 - t0 < 4 ? b0 - t0 : 4;
         if ((int)threadIdx.x < nt * GPT) {
             const int tt = threadIdx.x / GPT, gq = threadIdx.x - tt * GPT, pg = tile * GPT + gq;
             if (pg < npn) {
                 double sr = 0.0, si = 0.0;
-                for (int s = 0; s < nsub; ++s)
-                    for (int cc = 0; cc < NCOL; ++cc) {
-                        const double2 v = red[tt + s * b0][gq * NCOL + cc];
-                        sr += v.x;
-                        si += v.y;
-                    }
+                for (int s = 0; s < nsub; ++s) {
+                    const double2 v = red[tt + s * b0][gq];
+                    sr += v.x;
+                    si += v.y;
+                }
                 const int pp = pg / nsrc, ns = pg - pp * nsrc, x0 = y0 * b0 + t0 + tt;
                 part[((((size_t)(pair0 + pp) * nsrc + ns) * g.L[0] + x0) * LV_MAXCHUNK) + ch] =
                     make_double2(scale * sr, scale * si);
@@ -345,15 +386,16 @@ static int slice_partials_k(mglma_ctx* c, double scale, int nsrc, int nfine, int
         constexpr int GPT = 16 / (4 * NCS);
         const int npn = (npair - nfine) * nsrc;
         const dim3 grid(site_tile_grid((long)g.L1[0] * nchc, (npn + GPT - 1) / GPT));
-#define LV_COARSE(RT)                                                                                          \
-    hipLaunchKernelGGL((k_coarse_slice_part<NCS, SAME, RT>), grid, dim3(256), 0, c->stream, g, c->Nv, nchc, nsrc, \
+#define LV_COARSE(NS)                                                                                          \
+    hipLaunchKernelGGL((k_coarse_slice_part<NCS, SAME, NS>), grid, dim3(256), 0, c->stream, g, c->Nv, nchc, nsrc, \
                        npn, nfine, (const double2*)c->G1, Q, scale, part)
-        switch ((c->Nv + 15) / 16) {
-            case 1: LV_COARSE(1); break;
-            case 2: LV_COARSE(2); break;
-            case 3: LV_COARSE(3); break;
-            default: LV_COARSE(4); break;
-        }
+        const int ns = (c->Nv + 3) / 4;
+        if (ns <= 2) LV_COARSE(2);
+        else if (ns <= 4) LV_COARSE(4);
+        else if (ns <= 6) LV_COARSE(6);
+        else if (ns <= 8) LV_COARSE(8);
+        else if (ns <= 12) LV_COARSE(12);
+        else LV_COARSE(16);
 #undef LV_COARSE
         HIP_TRY(hipGetLastError());
     }

@@ -123,6 +123,23 @@ def test_contract_pair_cross_terms(pair):
     assert relerr(got, ref) < 1e-12
 
 
+# vectors: each number of unrolled steps of the coarse route, its tails, and two block extents in time
+@pytest.mark.parametrize("b,Nv", [((2, 2, 2, 2), 13), ((4, 2, 2, 2), 22), ((2, 2, 2, 2), 32), ((4, 2, 2, 2), 41),
+                                  ((2, 2, 2, 2), 64)])
+def test_coarse_pair_vectors(b, Nv):
+    """Coarse route of two different pieces and of a piece with itself, both kinds of source."""
+    P = Pair(tuple(2 * m for m in b), b, Nv, oracle_galerkin=False)
+    tn, nc = [1, 3], 2 * Nv
+    for kind, ncol, corr in ((POINT, 12, est.point_correlator),
+                             (STOCH, 4, lambda a, c, t: est.stochastic_pair(a, c, t, P.L))):
+        ca = synth.gaussian_coarse(ncol * 2, P.bl.V1, nc, 65)
+        cb = synth.gaussian_coarse(ncol * 2, P.bl.V1, nc, 66)
+        for q in (ca, cb):
+            ref = np.mean([corr(P.B.prolong(ca[ncol * n:ncol * n + ncol]), P.B.prolong(q[ncol * n:ncol * n + ncol]),
+                                tn[n]) for n in range(2)], axis=0)
+            assert relerr(P.ctx.contract_pair(kind, tn, to_dev(ca), to_dev(q), coarse=True), ref) < 1e-12
+
+
 def test_levels_chunked_slices():
     """A lattice whose time slices split into several chunks on both routes
     (4096 fine sites and 64 coarse sites per slice): random cumulative
