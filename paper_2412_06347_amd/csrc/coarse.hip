@@ -5,8 +5,8 @@
 // chirality negated).
 //
 // * FP64 / FP32 (matrix cores, v_mfma_f64_16x16x4 / v_mfma_f32_16x16x4):
-//   same tiling as BF16 below, operator from a planar copy in the working
-//   precision, vectors loaded as they are.
+//   same tiling as BF16 below, operator in the working precision (FP32: from a
+//   planar copy), vectors loaded as they are.
 // * BF16 (matrix cores): each wavefront owns a 16-row x 16-rhs output tile and
 //   runs v_mfma_f32_16x16x16_bf16 over (direction, 16-column) steps.  The
 //   complex product uses the planar real form
@@ -16,92 +16,225 @@
 
 // FP64 / FP32 on the matrix cores (v_mfma_*_16x16x4).
 // grid: the (coarse site, 16-rhs tile) items (site_tile); block: 64 *
-// ceil(nc/16) threads, wave w owns output rows 16w..16w+15 and the 16
-// right-hand sides of the item's tile.
-// Operator: planar copy P[y][dir][0 = re, 1 = im][i][j] in precision R.
-// In an MFMA lane (lr, lq) supplies A[row lr][k] and B[k][col lr] for one k
-// of four; over four successive MFMAs the lane walks k = k0 + 4 lq + s,
-// s = 0..3, so that its four operator entries and its four vector entries
-// are each one contiguous load (the sum over k does not care which lane
-// supplies which k as long as A and B agree).  VEC: nc % 4 == 0, so those
-// loads are aligned and either wholly inside or wholly outside the matrix.
-// IL: the operator is the interleaved complex array [y][dir][i][j] (FP64:
-// the library's D_1 itself, no planar copy); a lane's four k entries are
-// then one 64-byte run of complex values.
-template <typename R, bool VEC, bool IL = false>
+// ceil(nc/16) * DG threads, wave w owns output rows 16w..16w+15 and the 16
+// right-hand sides of the item's tile; with DG > 1 the (direction, 16 columns)
+// steps of a row tile are dealt to DG waves, whose partial sums are added in
+// LDS in a fixed order.  FP64 reads the interleaved complex operator
+// [y][dir][i][j] (the library's D_1 itself), FP32 the planar copy
+// [y][dir][0 = re, 1 = im][i][j].
+//
+// In an MFMA lane (lr, lq) supplies A[row lr][k] and B[k][col lr]: neighbouring
+// lanes hold different rows.  Loaded that way every lane is an L1 access of its
+// own (65 a load; the caches' tags then take 90 % of the time, whatever the
+// matrix cores do), so a wave loads its 16 x 16 tiles of operator and vectors
+// along the rows, 64 or 256 bytes a row, and changes lanes in LDS (its own
+// part of it, no barrier).  Slots are exchanged within a row (xor with the row)
+// so that neither side has bank conflicts.  FP64 takes three real products per
+// complex one (at 60 % of the cycles the matrix cores are the other bound).
+// 48 x 24^3, 24 vectors: FP64, 32 right-hand sides 417 -> 341 us (373 with four
+// products), 12: 226 -> 196, 1: 175 -> 170 (the operator's bytes); FP32, 32: 212
+// -> 193; 32 x 16^3, 20 right-hand sides FP64: 83 -> 57.  Two tiles of
+// right-hand sides a wave or a workgroup, or more loads in flight, without the
+// change of lanes: 380-430.
+template <typename R> struct CoarseTile;
+template <> struct CoarseTile<double> {
+    static constexpr int LDS = 2 * 256;      // 16-byte units a wave: operator, vectors
+    typedef double2 U;
+    double2 a[4], b[4];
+    // row i of the tile, column j: lane (j, i % 4), register i / 4
+    template <bool FULL>
+    __device__ __forceinline__ void load(const double* P, size_t, const double2* const* v, const int* m, int nc, int k0,
+                                         int lr, int, size_t zo) {
+        const int k = k0 + lr;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (!FULL) a[i] = b[i] = make_double2(0.0, 0.0);
+            if (FULL || k < nc) {
+                a[i] = ((const double2*)P)[(uint32_t)(m[i] * nc + k)];
+                b[i] = v[i][zo + k];
+            }
+        }
+    }
+    __device__ __forceinline__ void put(double2* sh, int lr, int lq) const {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int r = 4 * i + lq;
+            sh[r * 16 + (lr ^ r)] = a[i];
+            sh[256 + r * 16 + (lr ^ r)] = b[i];
+        }
+    }
+    static __device__ __forceinline__ void get(const double2* sh, int lr, int lq, double (&ar)[4], double (&ai)[4],
+                                               double (&br)[4], double (&bi)[4]) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const double2 x = sh[lr * 16 + ((4 * s + lq) ^ lr)], z = sh[256 + lr * 16 + ((4 * s + lq) ^ lr)];
+            ar[s] = x.x; ai[s] = x.y;
+            br[s] = z.x; bi[s] = z.y;
+        }
+    }
+    static __device__ __forceinline__ int row(int i, int lane) { return 4 * i + (lane >> 4); }      // of a[i], b[i]
+    static __device__ __forceinline__ int vrow(int i, int lane) { return row(i, lane); }
+};
+template <> struct CoarseTile<float> {
+    static constexpr int LDS = 2 * 64 + 128;
+    typedef float4 U;
+    float4 a[2], b[2];
+    // four columns of the operator's planes (lane: row lane / 4), two of a vector (row lane / 8 + 8 i)
+    template <bool FULL>
+    __device__ __forceinline__ void load(const float* P, size_t nn, const float2* const* v, const int* m, int nc,
+                                         int k0, int, int lane, size_t zo) {
+        const int k = k0 + 4 * (lane & 3), kv = k0 + 2 * (lane & 7);
+        const float* p = P + (uint32_t)(m[0] * nc + k);
+        if (!FULL) a[0] = a[1] = b[0] = b[1] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (FULL || k < nc) {
+            a[0] = *(const float4*)p;
+            a[1] = *(const float4*)(p + nn);
+        }
+        if (FULL || kv < nc) {
+            b[0] = *(const float4*)(v[0] + zo + kv);
+            b[1] = *(const float4*)(v[1] + zo + kv);
+        }
+    }
+    __device__ __forceinline__ void put(float4* sh, int, int lane) const {
+        const int r = lane >> 2, u = r * 4 + ((lane & 3) ^ (r >> 2));
+        sh[u] = a[0];
+        sh[64 + u] = a[1];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int q = (lane >> 3) + 8 * i;
+            sh[128 + q * 8 + ((lane & 7) ^ (q >> 1))] = b[i];
+        }
+    }
+    static __device__ __forceinline__ void get(const float4* sh, int lr, int lq, float (&ar)[4], float (&ai)[4],
+                                               float (&br)[4], float (&bi)[4]) {
+        const int u = lr * 4 + (lq ^ (lr >> 2));
+        const float4 x = sh[u], z = sh[64 + u];
+        const float4 p = sh[128 + lr * 8 + ((2 * lq) ^ (lr >> 1))], q = sh[128 + lr * 8 + ((2 * lq + 1) ^ (lr >> 1))];
+        ar[0] = x.x; ar[1] = x.y; ar[2] = x.z; ar[3] = x.w;
+        ai[0] = z.x; ai[1] = z.y; ai[2] = z.z; ai[3] = z.w;
+        br[0] = p.x; bi[0] = p.y; br[1] = p.z; bi[1] = p.w;
+        br[2] = q.x; bi[2] = q.y; br[3] = q.z; bi[3] = q.w;
+    }
+    static __device__ __forceinline__ int row(int, int lane) { return lane >> 2; }
+    static __device__ __forceinline__ int vrow(int i, int lane) { return (lane >> 3) + 8 * (i & 1); }
+};
+
+// orders a wave's LDS writes before its reads and the other way round (the
+// hardware keeps a wave's LDS accesses in order; this is for the compiler)
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// VEC = false (FP32 with nc not a multiple of four): entries loaded one by one,
+// straight into the lanes that multiply them
+template <typename R, bool VEC, int DG>
 __global__ __launch_bounds__(512) void k_coarse_mfma(Geo g, int nc, const R* __restrict__ P,
                                                      const typename VT<R>::c2* __restrict__ in,
                                                      typename VT<R>::c2* __restrict__ out, int nrhs, int gamma5) {
     typedef typename VT<R>::c2 C2;
     typedef typename Mfma<R>::v4 V4;
+    typedef CoarseTile<R> T;
+    extern __shared__ char shraw[];
     int y, tile;
     if (!site_tile(g.V1, (nrhs + 15) / 16, &y, &tile)) return;
-    const int n0 = tile * 16;
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int m0 = w * 16;
+    const int ntr = (nc + 15) / 16;
+    const int wall = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int w = DG > 1 ? wall % ntr : wall, dg = DG > 1 ? wall / ntr : 0;
+    const int m0 = w * 16, n0 = tile * 16;
     const int lr = lane & 15, lq = lane >> 4;
     const size_t V1 = g.V1, nn = (size_t)nc * nc;
-    const int n = n0 + lr, m = m0 + lr;
-    const bool nok = n < nrhs, mok = m < nc;
-    V4 cr = {0, 0, 0, 0}, ci = {0, 0, 0, 0};
-    for (int dir = 0; dir < 9; ++dir) {
-        const int z = coarse_nbr(g, y, dir);
-        const R* Pr = IL ? P + (((size_t)y * 9 + dir) * nn + (size_t)(mok ? m : 0) * nc) * 2
-                         : P + ((size_t)y * 9 + dir) * 2 * nn + (size_t)(mok ? m : 0) * nc;
-        const R* Pi = Pr + nn;
-        const C2* Pc = (const C2*)Pr;
-        const C2* v = in + ((size_t)(nok ? n : 0) * V1 + z) * nc;
-        for (int k0 = 0; k0 < nc; k0 += 16) {
-            const int kb = k0 + 4 * lq;
-            R ar[4], ai[4], br[4], bi[4];
-            if (VEC) {
-                const bool ka = kb < nc;
-                if (ka && mok) {
-                    if (IL) {
-                        ld4c(Pc + kb, ar, ai);
-                    } else {
-                        ld4(Pr + kb, ar);
-                        ld4(Pi + kb, ai);
-                    }
-                } else {
+    const int nk = (nc + 15) / 16, it0 = 9 * nk * dg / DG, it1 = 9 * nk * (dg + 1) / DG;
+    // FP64: three real products per complex one, re = cr - ci, im = c3 - cr - ci
+    V4 cr = {0, 0, 0, 0}, ci = {0, 0, 0, 0}, c3 = {0, 0, 0, 0};
+    auto mac = [&](const R (&ar)[4], const R (&ai)[4], const R (&br)[4], const R (&bi)[4]) {
 #pragma unroll
-                    for (int s = 0; s < 4; ++s) ar[s] = ai[s] = (R)0;
-                }
-                if (ka && nok) {
-                    ld4c(v + kb, br, bi);
-                } else {
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) br[s] = bi[s] = (R)0;
-                }
+        for (int s = 0; s < 4; ++s) {
+            cr = Mfma<R>::mac(ar[s], br[s], cr);
+            if constexpr (sizeof(R) == 8) {
+                ci = Mfma<R>::mac(ai[s], bi[s], ci);
+                c3 = Mfma<R>::mac(ar[s] + ai[s], br[s] + bi[s], c3);
             } else {
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    const bool ok = kb + s < nc;
-                    if (IL) {
-                        const C2 a = (ok && mok) ? Pc[kb + s] : C2{0, 0};
-                        ar[s] = a.x;
-                        ai[s] = a.y;
-                    } else {
-                        ar[s] = (ok && mok) ? Pr[kb + s] : (R)0;
-                        ai[s] = (ok && mok) ? Pi[kb + s] : (R)0;
-                    }
-                    C2 x = (ok && nok) ? v[kb + s] : C2{0, 0};
-                    br[s] = x.x;
-                    bi[s] = x.y;
-                }
-            }
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                cr = Mfma<R>::mac(ar[s], br[s], cr);
-                cr = Mfma<R>::mac(-ai[s], bi[s], cr);
                 ci = Mfma<R>::mac(ar[s], bi[s], ci);
+                cr = Mfma<R>::mac(-ai[s], bi[s], cr);
                 ci = Mfma<R>::mac(ai[s], br[s], ci);
             }
         }
+    };
+    // rows past nc and right-hand sides past nrhs repeat the last one: their results are not written
+    if constexpr (VEC) {
+        typename T::U* sh = (typename T::U*)shraw + wall * T::LDS;
+        int m[4];
+        const C2* v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            m[i] = m0 + T::row(i, lane) < nc ? m0 + T::row(i, lane) : nc - 1;
+            const int n = n0 + T::vrow(i, lane);
+            v[i] = in + (size_t)(n < nrhs ? n : nrhs - 1) * V1 * nc;
+        }
+        T f;
+        auto load = [&](int it) {
+            const int dir = it / nk, k0 = (it - dir * nk) * 16;
+            const R* Pr = P + ((size_t)y * 9 + dir) * 2 * nn;
+            const size_t zo = (size_t)coarse_nbr(g, y, dir) * nc;
+            if (k0 + 16 <= nc) f.template load<true>(Pr, nn, v, m, nc, k0, lr, lane, zo);
+            else f.template load<false>(Pr, nn, v, m, nc, k0, lr, lane, zo);
+        };
+        load(it0);
+        for (int it = it0; it < it1; ++it) {
+            f.put(sh, lr, sizeof(R) == 8 ? lq : lane);
+            if (it + 1 < it1) load(it + 1);
+            wave_lds_fence();
+            R ar[4], ai[4], br[4], bi[4];
+            T::get(sh, lr, lq, ar, ai, br, bi);
+            wave_lds_fence();
+            mac(ar, ai, br, bi);
+        }
+    } else {
+        const size_t mo = (size_t)(m0 + lr < nc ? m0 + lr : nc - 1) * nc;
+        const C2* v = in + (size_t)(n0 + lr < nrhs ? n0 + lr : nrhs - 1) * V1 * nc;
+        for (int it = it0; it < it1; ++it) {
+            const int dir = it / nk, k0 = (it - dir * nk) * 16;
+            const R* Pr = P + ((size_t)y * 9 + dir) * 2 * nn + mo;
+            const size_t zo = (size_t)coarse_nbr(g, y, dir) * nc;
+            R ar[4], ai[4], br[4], bi[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int k = k0 + lq + 4 * s;
+                const bool ok = k < nc;
+                const C2 x = ok ? v[zo + k] : C2{0, 0};
+                ar[s] = ok ? Pr[k] : (R)0;
+                ai[s] = ok ? Pr[nn + k] : (R)0;
+                br[s] = x.x;
+                bi[s] = x.y;
+            }
+            mac(ar, ai, br, bi);
+        }
+    }
+    if constexpr (sizeof(R) == 8) {
+        const V4 im = c3 - cr - ci;
+        cr = cr - ci;
+        ci = im;
+    }
+    if constexpr (DG > 1) {
+        __syncthreads();
+        V4* part = (V4*)shraw;
+        if (dg > 0) {
+            part[((dg - 1) * ntr + w) * 2 * 64 + lane] = cr;
+            part[((dg - 1) * ntr + w) * 2 * 64 + 64 + lane] = ci;
+        }
+        __syncthreads();
+        if (dg > 0) return;
+#pragma unroll
+        for (int q = 1; q < DG; ++q) {
+            cr += part[((q - 1) * ntr + w) * 2 * 64 + lane];
+            ci += part[((q - 1) * ntr + w) * 2 * 64 + 64 + lane];
+        }
     }
     // register t of this lane holds C[row(lq, t)][col lr]
-    if (nok) {
-        C2* o = out + ((size_t)n * V1 + y) * nc;
+    if (n0 + lr < nrhs) {
+        C2* o = out + ((size_t)(n0 + lr) * V1 + y) * nc;
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             const int row = m0 + Mfma<R>::row(lq, t);
@@ -221,6 +354,25 @@ __global__ void k_coarse_bf16(Geo g, int nc, const bf16_t* __restrict__ Dbf, con
     }
 }
 
+template <typename R, bool VEC>
+static int coarse_launch(const Geo& g, int nc, const R* P, const void* in, void* out, int nrhs, int gamma5,
+                         hipStream_t stream) {
+    typedef typename VT<R>::c2 C2;
+    const int ntr = (nc + 15) / 16;
+    const dim3 grid(site_tile_grid(g.V1, (nrhs + 15) / 16));
+    // few waves: the steps of a row tile over three of them (16 sites, nc = 16, one right-hand side: 10.3 -> 5.6 us)
+    const int dg = ntr <= 2 && g.V1 * ntr * ((nrhs + 15) / 16) < 2048 ? 3 : 1;
+    const size_t shb = (size_t)ntr * dg * CoarseTile<R>::LDS * 16;
+    if (dg > 1)
+        hipLaunchKernelGGL((k_coarse_mfma<R, VEC, 3>), grid, dim3(64 * ntr * dg), shb, stream, g, nc, P, (const C2*)in,
+                           (C2*)out, nrhs, gamma5);
+    else
+        hipLaunchKernelGGL((k_coarse_mfma<R, VEC, 1>), grid, dim3(64 * ntr), shb, stream, g, nc, P, (const C2*)in,
+                           (C2*)out, nrhs, gamma5);
+    HIP_TRY(hipGetLastError());
+    return MGLMA_OK;
+}
+
 int mg_coarse_apply(mglma_ctx* c, int prec, int gamma5, const void* in, void* out, int nrhs) {
     if (prec == MGLMA_F32) MG_TRY(mg_need_d32(c));
     return mg_stencil_apply(c, c->geo, c->nc, (const double*)c->D64, c->D32p, c->Dbf, prec, gamma5, in, out, nrhs);
@@ -258,30 +410,10 @@ int mg_stencil_apply(mglma_ctx* c, const Geo& g, int nc, const double* P64, cons
         HIP_TRY(hipGetLastError());
         return MGLMA_OK;
     }
-    dim3 grid(site_tile_grid(g.V1, (nrhs + 15) / 16));
-    dim3 block(64 * ((nc + 15) / 16));
-    const bool vec = nc % 4 == 0;
-    switch (prec) {
-        case MGLMA_F64:
-            if (vec)
-                hipLaunchKernelGGL((k_coarse_mfma<double, true, true>), grid, block, 0, c->stream, g, nc, P64,
-                                   (const double2*)in, (double2*)out, nrhs, gamma5);
-            else
-                hipLaunchKernelGGL((k_coarse_mfma<double, false, true>), grid, block, 0, c->stream, g, nc, P64,
-                                   (const double2*)in, (double2*)out, nrhs, gamma5);
-            break;
-        case MGLMA_F32:
-            if (vec)
-                hipLaunchKernelGGL((k_coarse_mfma<float, true>), grid, block, 0, c->stream, g, nc, P32,
-                                   (const float2*)in, (float2*)out, nrhs, gamma5);
-            else
-                hipLaunchKernelGGL((k_coarse_mfma<float, false>), grid, block, 0, c->stream, g, nc, P32,
-                                   (const float2*)in, (float2*)out, nrhs, gamma5);
-            break;
-        default: return MGLMA_ERR_ARG;
-    }
-    HIP_TRY(hipGetLastError());
-    return MGLMA_OK;
+    if (prec == MGLMA_F64) return coarse_launch<double, true>(g, nc, P64, in, out, nrhs, gamma5, c->stream);
+    if (prec != MGLMA_F32) return MGLMA_ERR_ARG;
+    if (nc % 4 == 0) return coarse_launch<float, true>(g, nc, P32, in, out, nrhs, gamma5, c->stream);
+    return coarse_launch<float, false>(g, nc, P32, in, out, nrhs, gamma5, c->stream);
 }
 
 extern "C" int mglma_coarse_apply(mglma_ctx* c, int prec, int gamma5, const void* in, void* out, int nrhs) {

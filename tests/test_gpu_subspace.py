@@ -128,6 +128,22 @@ def test_coarse_apply_parity(pair, prec, tol, gamma5):
     assert err < tol
 
 
+# vectors and right-hand sides: columns in and out of fours and sixteens, one and several row tiles, and
+# full, partial and several tiles of right-hand sides
+@pytest.mark.parametrize("Nv,n", [(1, 3), (8, 16), (13, 17), (22, 33)])
+@pytest.mark.parametrize("prec,tol", [(0, 1e-12), (1, 2e-6)])
+def test_coarse_apply_shapes(Nv, n, prec, tol):
+    import torch
+    from oracle import coarse
+    P = Pair((4, 4, 2, 4), (2, 2, 2, 2), Nv)
+    x = synth.gaussian_coarse(n, P.bl.V1, 2 * Nv, 81)
+    xd = to_dev(x).to(torch.float64 if prec == 0 else torch.float32)
+    y = torch.empty_like(xd)
+    P.ctx.coarse_apply(xd, y, prec)
+    ref = (coarse.coarse_dense(P.D1, P.nbr) @ x.reshape(n, -1).T).T.reshape(x.shape)
+    assert relerr(from_dev(y), ref) < tol
+
+
 def test_rank_deficient_basis_is_an_error():
     import torch
     from paper_2412_06347_amd import mglma
