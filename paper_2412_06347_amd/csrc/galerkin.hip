@@ -227,7 +227,11 @@ __global__ __launch_bounds__(256) void k_galerkin_piece(Geo g, int Nv, const dou
 // T1 = Re L Re R, T2 = Im L Im R, T3 = (Re L + Im L)(Re R + Im R), then
 // Re = T1 - T2 and Im = T3 - T1 - T2.  GF is even so that 6 GF rows are
 // whole k-steps of four.  Register budget: three wavefronts per SIMD (two for
-// four output stripes), measured fastest at n_c = 48.
+// four output stripes), measured fastest at n_c = 48.  The nine pieces of a
+// block run back to back on one XCD: they read the same basis vectors, 25 GB
+// through the caches on 48 x 24^3 for a basis of 2 GB (10.1 -> 8.4 ms there).
+// Loads of the next sites' vectors during the products spill at three
+// wavefronts per SIMD (11 ms), and at two leave the SIMDs unevenly filled (9.5).
 template <int NTR>
 __global__ __launch_bounds__(64 * NTR) __attribute__((amdgpu_waves_per_eu(NTR <= 3 ? 3 : 2)))
 void k_galerkin_mfma3(Geo g, int Nv, const double2* __restrict__ B, const double2* __restrict__ U,
@@ -235,7 +239,9 @@ void k_galerkin_mfma3(Geo g, int Nv, const double2* __restrict__ B, const double
                       double2* __restrict__ tmp) {
     typedef Mfma<double>::v4 V4;
     extern __shared__ double2 sh[];
-    const int y = blockIdx.x, piece = gal_piece(blockIdx.y);
+    int y, pidx;
+    if (!site_tile(g.V1, GAL_NPIECE, &y, &pidx)) return;
+    const int piece = gal_piece(pidx);
     const int nc = 2 * Nv, ncp = 16 * NTR;
     double2* Lh = sh;                                  // [GF][6][ncp]
     double2* Rh = sh + (size_t)GF * 6 * ncp;           // [GF][6][ncp]
@@ -339,7 +345,7 @@ int mg_galerkin(mglma_ctx* c, double2* tmp) {
         if (GF > gmax) GF = gmax;
         if (GF < 2) GF = 2;
         const size_t shb = (size_t)2 * GF * 6 * ncp * sizeof(double2);
-        dim3 grid(g.V1, GAL_NPIECE);
+        dim3 grid(site_tile_grid(g.V1, GAL_NPIECE));
 #define GALM_LAUNCH(NTR)                                                                                        \
     hipLaunchKernelGGL((k_galerkin_mfma3<NTR>), grid, dim3(64 * NTR), shb, c->stream, g, c->Nv, c->B64, c->U64, \
                        c->C64, c->kappa, GF, c->D64, tmp)
