@@ -371,33 +371,39 @@ __device__ __forceinline__ void m3_add(M3& a, const M3& b) {
     for (int k = 0; k < 9; ++k) a.e[k] = a.e[k] + b.e[k];
 }
 
-// link U_mu at x + d1*e_{m1} + d2*e_{m2}
-__device__ M3 link_at(const Geo& g, const double2* U, const int x[4], int mu, int m1, int d1, int m2, int d2) {
+// links U_mu(x), U_mu(x + d e_M) and U_mu(x + d1 e_MU + d2 e_NU)
+template <int MU, int NU>
+__device__ __forceinline__ M3 link_at(const Geo& g, const double2* U, const int x[4], int mu, int d1, int d2) {
     int y[4] = {x[0], x[1], x[2], x[3]};
-    y[m1] = (y[m1] + d1 + g.L[m1]) % g.L[m1];
-    y[m2] = (y[m2] + d2 + g.L[m2]) % g.L[m2];
+    y[MU] += d1;
+    y[MU] = y[MU] == g.L[MU] ? 0 : y[MU] < 0 ? g.L[MU] - 1 : y[MU];
+    y[NU] += d2;
+    y[NU] = y[NU] == g.L[NU] ? 0 : y[NU] < 0 ? g.L[NU] - 1 : y[NU];
     return m3_load(U, g.V, mu, geo_index(g, y));
 }
 
-// F_{mu nu}(x): traceless part of (Q - Q^+)/8
-__device__ M3 field_strength(const Geo& g, const double2* U, const int x[4], int mu, int nu) {
-    M3 Um = link_at(g, U, x, mu, mu, 0, nu, 0);
-    M3 Un = link_at(g, U, x, nu, mu, 0, nu, 0);
+// F_{mu nu}(x): traceless part of (Q - Q^+)/8, the leaves' products from left
+// to right (two matrices live next to the sum)
+template <int MU, int NU>
+__device__ __forceinline__ M3 field_strength(const Geo& g, const double2* U, const int x[4]) {
+#define LK(mu, d1, d2) link_at<MU, NU>(g, U, x, mu, d1, d2)
     // leaf 1: U_mu(x) U_nu(x+mu) U_mu(x+nu)^+ U_nu(x)^+
-    M3 q = m3_mul(m3_mul(Um, link_at(g, U, x, nu, mu, 1, nu, 0)),
-                  m3_mul(m3_dag(link_at(g, U, x, mu, mu, 0, nu, 1)), m3_dag(Un)));
+    M3 q = m3_mul(LK(MU, 0, 0), LK(NU, 1, 0));
+    q = m3_mul(q, m3_dag(LK(MU, 0, 1)));
+    q = m3_mul(q, m3_dag(LK(NU, 0, 0)));
     // leaf 2: U_nu(x) U_mu(x+nu-mu)^+ U_nu(x-mu)^+ U_mu(x-mu)
-    M3 t = m3_mul(m3_mul(Un, m3_dag(link_at(g, U, x, mu, mu, -1, nu, 1))),
-                  m3_mul(m3_dag(link_at(g, U, x, nu, mu, -1, nu, 0)), link_at(g, U, x, mu, mu, -1, nu, 0)));
-    m3_add(q, t);
+    M3 t = m3_mul(LK(NU, 0, 0), m3_dag(LK(MU, -1, 1)));
+    t = m3_mul(t, m3_dag(LK(NU, -1, 0)));
+    m3_add(q, m3_mul(t, LK(MU, -1, 0)));
     // leaf 3: U_mu(x-mu)^+ U_nu(x-mu-nu)^+ U_mu(x-mu-nu) U_nu(x-nu)
-    t = m3_mul(m3_mul(m3_dag(link_at(g, U, x, mu, mu, -1, nu, 0)), m3_dag(link_at(g, U, x, nu, mu, -1, nu, -1))),
-               m3_mul(link_at(g, U, x, mu, mu, -1, nu, -1), link_at(g, U, x, nu, mu, 0, nu, -1)));
-    m3_add(q, t);
+    t = m3_mul(m3_dag(LK(MU, -1, 0)), m3_dag(LK(NU, -1, -1)));
+    t = m3_mul(t, LK(MU, -1, -1));
+    m3_add(q, m3_mul(t, LK(NU, 0, -1)));
     // leaf 4: U_nu(x-nu)^+ U_mu(x-nu) U_nu(x+mu-nu) U_mu(x)^+
-    t = m3_mul(m3_mul(m3_dag(link_at(g, U, x, nu, mu, 0, nu, -1)), link_at(g, U, x, mu, mu, 0, nu, -1)),
-               m3_mul(link_at(g, U, x, nu, mu, 1, nu, -1), m3_dag(Um)));
-    m3_add(q, t);
+    t = m3_mul(m3_dag(LK(NU, 0, -1)), LK(MU, 0, -1));
+    t = m3_mul(t, LK(NU, 1, -1));
+    m3_add(q, m3_mul(t, m3_dag(LK(MU, 0, 0))));
+#undef LK
     M3 F;
 #pragma unroll
     for (int i = 0; i < 3; ++i)
@@ -411,50 +417,89 @@ __device__ M3 field_strength(const Geo& g, const double2* U, const int x[4], int
     return F;
 }
 
-__global__ void k_build_clover(Geo g, const double2* __restrict__ U, double kc, double2* __restrict__ C64,
-                               float2* __restrict__ C32, __half2* __restrict__ C16) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= g.V) return;
-    int lc[4], yc[4], x[4];
-    geo_coords(g, i, lc, yc);
-    for (int mu = 0; mu < 4; ++mu) x[mu] = yc[mu] * g.b[mu] + lc[mu];
-    M3 F01 = field_strength(g, U, x, 0, 1), F02 = field_strength(g, U, x, 0, 2), F03 = field_strength(g, U, x, 0, 3);
-    M3 F12 = field_strength(g, U, x, 1, 2), F13 = field_strength(g, U, x, 1, 3), F23 = field_strength(g, U, x, 2, 3);
-    size_t V = g.V;
-    for (int ch = 0; ch < 2; ++ch) {
-        double sg = ch == 0 ? 1.0 : -1.0;
-        M3 E1, E2, E3;
-        for (int k = 0; k < 9; ++k) {
-            E1.e[k] = sg * F01.e[k] - F23.e[k];
-            E2.e[k] = sg * F02.e[k] + F13.e[k];
-            E3.e[k] = sg * F03.e[k] - F12.e[k];
-        }
-        // 6x6 block A[3s+a][3t+b], s,t in {0,1}
-        cx<double> A[6][6];
-        for (int a = 0; a < 3; ++a)
-            for (int b2 = 0; b2 < 3; ++b2) {
-                cx<double> e1 = E1.e[a * 3 + b2], e2 = E2.e[a * 3 + b2], e3 = E3.e[a * 3 + b2];
-                // i kc * (sigma_l)_{st} E_l
-                A[a][b2] = kc * mul_i(e3);
-                A[3 + a][3 + b2] = kc * mul_i(-e3);
-                A[a][3 + b2] = kc * mul_i(e1 - mul_i(e2));
-                A[3 + a][b2] = kc * mul_i(e1 + mul_i(e2));
-            }
-        for (int m = 0; m < 6; ++m) A[m][m].re += 1.0;
-        double2* c64 = C64 + (size_t)ch * 18 * V;
-        float2* c32 = C32 + (size_t)ch * 18 * V;
-        __half2* c16 = C16 + (size_t)ch * 18 * V;
-        cx<double> slot[18];
-        for (int m = 0; m < 3; ++m) slot[m] = cmk(A[2 * m][2 * m].re, A[2 * m + 1][2 * m + 1].re);
-        int k = 3;
-        for (int r = 0; r < 6; ++r)
-            for (int cc = r + 1; cc < 6; ++cc) slot[k++] = A[r][cc];
-        for (int s = 0; s < 18; ++s) {
-            c64[(size_t)s * V + i] = make_double2(slot[s].re, slot[s].im);
-            c32[(size_t)s * V + i] = make_float2((float)slot[s].re, (float)slot[s].im);
-            c16[(size_t)s * V + i] = __floats2half2_rn((float)slot[s].re, (float)slot[s].im);
-        }
+#define CL_SITES 64
+// entry (R, C), R <= C, of 1 + i kc sigma_l E_l in block form A[3s+a][3t+b], s, t in {0, 1};
+// F: field strengths of the site in LDS, planes 01, 02, 03, 12, 13, 23
+template <int R, int C>
+__device__ __forceinline__ cx<double> clover_entry(const double2* F, double sg, double kc) {
+    constexpr int ab = R % 3 * 3 + C % 3;
+    auto f = [&](int p) { return ldc<double2, double>(F + (p * 9 + ab) * CL_SITES); };
+    cx<double> v;
+    if (R / 3 == C / 3) {
+        const cx<double> e3 = sg * f(2) - f(3);
+        v = kc * mul_i(R / 3 ? -e3 : e3);
+    } else {
+        const cx<double> e1 = sg * f(0) - f(5), e2 = sg * f(1) + f(4);
+        v = kc * mul_i(e1 - mul_i(e2));
     }
+    if (R == C) v.re += 1.0;
+    return v;
+}
+
+// Clover term and its copies.  One workgroup per 64 sites, one wavefront per
+// plane: F of the six planes goes to LDS, then every wavefront packs six of the
+// 36 entries of its sites (chirality w / 3).  One thread per site and all six
+// planes in turn had too few wavefronts to cover its loads: 2.28 ms on 48 x 24^3,
+// 0.68 here (load of a gauge field 2.65 -> 1.05); held to 168 registers it takes
+// 1.07.
+__global__ __launch_bounds__(384) void k_build_clover(Geo g, const double2* __restrict__ U, double kc,
+                                                      double2* __restrict__ C64, float2* __restrict__ C32,
+                                                      __half2* __restrict__ C16) {
+    __shared__ double2 Fs[6 * 9 * CL_SITES];
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int i0 = blockIdx.x * CL_SITES + lane, i = i0 < g.V ? i0 : g.V - 1;
+    {
+        int lc[4], yc[4], x[4];
+        geo_coords(g, i, lc, yc);
+        for (int mu = 0; mu < 4; ++mu) x[mu] = yc[mu] * g.b[mu] + lc[mu];
+        M3 F;
+        switch (w) {
+            case 0: F = field_strength<0, 1>(g, U, x); break;
+            case 1: F = field_strength<0, 2>(g, U, x); break;
+            case 2: F = field_strength<0, 3>(g, U, x); break;
+            case 3: F = field_strength<1, 2>(g, U, x); break;
+            case 4: F = field_strength<1, 3>(g, U, x); break;
+            default: F = field_strength<2, 3>(g, U, x); break;
+        }
+#pragma unroll
+        for (int k = 0; k < 9; ++k) Fs[(w * 9 + k) * CL_SITES + lane] = make_double2(F.e[k].re, F.e[k].im);
+    }
+    __syncthreads();
+    if (i0 >= g.V) return;
+    const int ch = w / 3, part = w - 3 * ch;
+    const double sg = ch == 0 ? 1.0 : -1.0;
+    const double2* F = Fs + lane;
+    const size_t V = g.V;
+    auto put = [&](int s, cx<double> v) {
+        const size_t o = ((size_t)ch * 18 + s) * V + i;
+        C64[o] = make_double2(v.re, v.im);
+        C32[o] = make_float2((float)v.re, (float)v.im);
+        C16[o] = __floats2half2_rn((float)v.re, (float)v.im);
+    };
+#define CE(r, c) clover_entry<r, c>(F, sg, kc)
+    if (part == 0) {
+        put(0, cmk(CE(0, 0).re, CE(1, 1).re));
+        put(1, cmk(CE(2, 2).re, CE(3, 3).re));
+        put(2, cmk(CE(4, 4).re, CE(5, 5).re));
+        put(3, CE(0, 1));
+        put(4, CE(0, 2));
+        put(5, CE(0, 3));
+    } else if (part == 1) {
+        put(6, CE(0, 4));
+        put(7, CE(0, 5));
+        put(8, CE(1, 2));
+        put(9, CE(1, 3));
+        put(10, CE(1, 4));
+        put(11, CE(1, 5));
+    } else {
+        put(12, CE(2, 3));
+        put(13, CE(2, 4));
+        put(14, CE(2, 5));
+        put(15, CE(3, 4));
+        put(16, CE(3, 5));
+        put(17, CE(4, 5));
+    }
+#undef CE
 }
 
 extern "C" int mglma_load_gauge(mglma_ctx* c, const double* U_dev) {
@@ -480,7 +525,7 @@ extern "C" int mglma_load_gauge(mglma_ctx* c, const double* U_dev) {
     HIP_TRY(hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     if (hbad) { c->have_gauge = false; return MGLMA_ERR_NONFINITE; }
-    hipLaunchKernelGGL(k_build_clover, dim3((g.V + 127) / 128), dim3(128), 0, c->stream, g, (const double2*)c->U64,
+    hipLaunchKernelGGL(k_build_clover, dim3((g.V + CL_SITES - 1) / CL_SITES), dim3(384), 0, c->stream, g, (const double2*)c->U64,
                        c->kappa * c->csw, c->C64, c->C32, c->C16);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(c->stream));

@@ -40,6 +40,12 @@ def test_clover_parity(case):
     assert np.abs(got - ref).max() < 1e-13
 
 
+@pytest.mark.parametrize("L", [(3, 1, 2, 5), (2, 2, 2, 2), (5, 13, 1, 2)])
+def test_clover_small_extents(L):
+    """Less than a workgroup of sites, a partial second one, and extents of one and two."""
+    test_clover_parity((L, L, 0.12, 1.1, 0.3))
+
+
 @pytest.mark.parametrize("case", CASES)
 @pytest.mark.parametrize("gamma5", [0, 1])
 def test_apply_parity(case, gamma5):
