@@ -119,14 +119,6 @@ template <> struct CoarseTile<float> {
     static __device__ __forceinline__ int vrow(int i, int lane) { return (lane >> 3) + 8 * (i & 1); }
 };
 
-// orders a wave's LDS writes before its reads and the other way round (the
-// hardware keeps a wave's LDS accesses in order; this is for the compiler)
-__device__ __forceinline__ void wave_lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // VEC = false (FP32 with nc not a multiple of four): entries loaded one by one,
 // straight into the lanes that multiply them
 template <typename R, bool VEC, int DG>

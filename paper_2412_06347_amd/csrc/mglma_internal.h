@@ -245,6 +245,14 @@ __device__ __forceinline__ void ld4c(const double2* p, double (&re)[4], double (
     }
 }
 
+// orders a wave's LDS writes before its reads and the other way round (the
+// hardware keeps a wave's LDS accesses in order; this is for the compiler)
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // In both, lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16]; result
 // register t of lane l is D[row(l / 16, t)][l % 16], and the two differ in
 // row(): 4 q + t for FP32, q + 4 t for FP64 (measured on gfx950).

@@ -25,64 +25,174 @@ int mg_galerkin(mglma_ctx* c, double2* tmp);
 // ---------------------------------------------------------------------------
 // basis construction
 // ---------------------------------------------------------------------------
-__global__ void k_tv_to_basis(Geo g, int Nv, const double2* __restrict__ tv, double2* __restrict__ B) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    int c = blockIdx.y;
-    if (i >= g.V) return;
-    int y = i / g.Vb, l = i - y * g.Vb;
-    size_t V = g.V, Vb = g.Vb;
-    for (int sc = 0; sc < 12; ++sc) {
-        int a = sc / 6, scl = sc % 6;
-        B[((((size_t)y * 2 + a) * Nv + c) * 6 + scl) * Vb + l] = tv[((size_t)c * 12 + sc) * V + i];
+// field offset of column k: s'col V + l
+__device__ __forceinline__ size_t col_off(int k, int Vb, size_t V) {
+    int s = 0;
+#pragma unroll
+    for (int m = 1; m < 6; ++m) s += k >= m * Vb;
+    return (size_t)s * (V - Vb) + (uint32_t)k;
+}
+
+// One pass of a Cholesky QR over sets of Nv vectors of K columns each, on the
+// FP64 matrix cores:
+//   APPLY: w_d = sum_{c <= d} src_c X[c][d], written to B (and its FP32 and FP16
+//          copies where given);
+//   GRAM:  G[c][d] = <w_c, w_d> for c <= d (without APPLY: of the source).
+// The source is B itself (in place: a wavefront has read all vectors of its 16
+// columns before it writes them) or, TV, the test vectors: set (y, a), column k
+// = (s'col, l) is component 6 a + s'col at site y Vb + l, so the first pass also
+// does the block projection and chiral split.
+// One workgroup per set, wavefronts over tiles of 16 columns, no barrier between
+// tiles.  APPLY: the rows of D = X^T W are vectors, its columns are contiguous in
+// memory for loads and stores; X lies in LDS in the order of the lanes, upper
+// triangle only.  GRAM: the tile goes through the wavefront's part of LDS (rows
+// in, fragments out, slots exchanged within a row against bank conflicts).
+//
+// Bound: memory (read, write) and, with both, as much the matrix cores.  The
+// three passes of a basis (Gram; apply and Gram; apply) on 48 x 24^3, 24
+// vectors: 1.0 + 1.9 + 1.8 ms (0.65 + 1.3 + 1.4 at the rate of a copy), against
+// 1.2 for the projection and twice 1.1 + 1.5 on the vector units, one pass each.
+template <int NTR, bool APPLY, bool GRAM, bool TV>
+__global__ __launch_bounds__(256) void k_qr_pass(Geo g, int Nv, int K, const double2* __restrict__ tv, double2* B,
+                                                 const double2* __restrict__ X, double2* __restrict__ G,
+                                                 float2* __restrict__ B32, __half2* __restrict__ B16) {
+    typedef Mfma<double> MF;
+    typedef MF::v4 V4;
+    constexpr int NS = 4 * NTR, NX = APPLY ? 2 * NTR * (NTR + 1) : 0, NP = NTR * (NTR + 1) / 2;
+    extern __shared__ double2 shx[];                   // X fragments, then the wavefronts' tiles
+    const int ya = blockIdx.x, w = threadIdx.x >> 6, nw = blockDim.x >> 6, lane = threadIdx.x & 63;
+    const int lr = lane & 15, lq = lane >> 4, ns = (Nv + 3) / 4;
+    double2* sh = shx + NX * 64 + (GRAM ? w * NTR * 256 : 0);
+    double2* Wb = B + (size_t)ya * Nv * K;
+    // source (c, k): S[c * cs + off(k)]
+    const double2* S = TV ? tv + (size_t)(ya & 1) * 6 * g.V + (size_t)(ya >> 1) * g.Vb : Wb;
+    const size_t cs = TV ? (size_t)12 * g.V : (size_t)K;
+    auto off = [&](int k) { return TV ? col_off(k, g.Vb, g.V) : (size_t)(uint32_t)k; };
+    if constexpr (APPLY) {
+        const double2* Xs = X + (size_t)ya * Nv * Nv;
+        for (int e = w; e < NX; e += nw) {
+            int t = 0;
+            while (2 * (t + 1) * (t + 2) <= e) ++t;
+            const int d = 16 * t + lr, c = 4 * (e - 2 * t * (t + 1)) + lq;
+            shx[e * 64 + lane] = c < Nv && d < Nv ? Xs[c * Nv + d] : make_double2(0.0, 0.0);
+        }
+        __syncthreads();
+    }
+    V4 gr[GRAM ? NP : 1], gi[GRAM ? NP : 1];
+#pragma unroll
+    for (int p = 0; p < (GRAM ? NP : 1); ++p) {
+        gr[p] = V4{0, 0, 0, 0};
+        gi[p] = V4{0, 0, 0, 0};
+    }
+    const int nt = (K + 15) / 16;
+    for (int q = w; q < nt; q += nw) {
+        const int k = 16 * q + lr;
+        const bool kok = k < K;
+        const size_t ko = kok ? off(k) : 0;
+        if constexpr (APPLY) {
+            double2 b[NS];
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                if (s < ns) {
+                    const int c = 4 * s + lq;
+                    b[s] = S[(size_t)(c < Nv ? c : Nv - 1) * cs + ko];
+                    b[s].x = kok ? b[s].x : 0.0;
+                    b[s].y = kok ? b[s].y : 0.0;
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < NTR; ++t) {
+                V4 dr = {0, 0, 0, 0}, di = {0, 0, 0, 0};
+#pragma unroll
+                for (int s = 0; s < 4 * (t + 1); ++s) {
+                    if (s < ns) {
+                        const double2 x = shx[(2 * t * (t + 1) + s) * 64 + lane];
+                        dr = MF::mac(x.x, b[s].x, dr);
+                        di = MF::mac(x.x, b[s].y, di);
+                        dr = MF::mac(-x.y, b[s].y, dr);
+                        di = MF::mac(x.y, b[s].x, di);
+                    }
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int i = MF::row(lq, r), d = 16 * t + i;
+                    const double2 v = make_double2(dr[r], di[r]);
+                    if (GRAM) sh[t * 256 + i * 16 + (lr ^ i)] = v;
+                    if (kok && d < Nv) {
+                        const size_t o = (size_t)d * K + k, og = (size_t)ya * Nv * K + o;
+                        Wb[o] = v;
+                        if (B32) B32[og] = make_float2((float)v.x, (float)v.y);
+                        if (B16) B16[og] = __floats2half2_rn((float)v.x, (float)v.y);
+                    }
+                }
+            }
+        } else {
+#pragma unroll
+            for (int t = 0; t < NTR; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int i = 4 * r + lq, c = 16 * t + i;
+                    double2 v = make_double2(0.0, 0.0);
+                    if (kok && c < Nv) v = S[(size_t)c * cs + ko];
+                    sh[t * 256 + i * 16 + (lr ^ i)] = v;
+                }
+        }
+        if constexpr (GRAM) {
+            wave_lds_fence();
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                double2 f[NTR];
+#pragma unroll
+                for (int t = 0; t < NTR; ++t) f[t] = sh[t * 256 + lr * 16 + ((4 * s + lq) ^ lr)];
+                int p = 0;
+#pragma unroll
+                for (int i = 0; i < NTR; ++i)
+#pragma unroll
+                    for (int j = i; j < NTR; ++j, ++p) {
+                        gr[p] = MF::mac(f[i].x, f[j].x, gr[p]);
+                        gi[p] = MF::mac(f[i].x, f[j].y, gi[p]);
+                        gr[p] = MF::mac(f[i].y, f[j].y, gr[p]);
+                        gi[p] = MF::mac(-f[i].y, f[j].x, gi[p]);
+                    }
+            }
+            wave_lds_fence();
+        }
+    }
+    if constexpr (GRAM) {
+        double* red = (double*)(shx + NX * 64);        // [wavefronts][re, im][64 lanes][4]
+        double2* Gs = G + (size_t)ya * Nv * Nv;
+        int p = 0;
+#pragma unroll
+        for (int i = 0; i < NTR; ++i)
+#pragma unroll
+            for (int j = i; j < NTR; ++j, ++p) {
+                __syncthreads();
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    red[w * 512 + lane * 4 + r] = gr[p][r];
+                    red[w * 512 + 256 + lane * 4 + r] = gi[p][r];
+                }
+                __syncthreads();
+                for (int e = threadIdx.x; e < 256; e += blockDim.x) {
+                    const int c = 16 * i + MF::row(e >> 6, e & 3), d = 16 * j + ((e >> 2) & 15);
+                    if (c > d || d >= Nv) continue;
+                    double sr = 0.0, si = 0.0;
+                    for (int ww = 0; ww < nw; ++ww) {
+                        sr += red[ww * 512 + e];
+                        si += red[ww * 512 + 256 + e];
+                    }
+                    Gs[c * Nv + d] = make_double2(sr, si);
+                }
+            }
     }
 }
 
-#define GCH 32   // k-chunk of the Gram kernel
-
-// G[(y,a)][c][d] = <w_c, w_d> for c <= d
-__global__ __launch_bounds__(256) void k_gram(const double2* __restrict__ B, int Nv, int K, double2* __restrict__ G) {
-    extern __shared__ double2 sh[];   // [Nv][GCH+1]
+// G (upper) = R^+ R; Rinv = R^{-1} (upper).  R is formed in LDS.
+__global__ void k_chol_inv(int Nv, const double2* __restrict__ G, double2* __restrict__ Rinv, double tol, int* bad) {
     const int ya = blockIdx.x;
-    const double2* W = B + (size_t)ya * Nv * K;
-    const int P = Nv * (Nv + 1) / 2;
-    const int np = (P + 255) / 256;   // pairs per thread (<= 9 for Nv <= 64)
-    cx<double> acc[9];
-    int pc[9], pd[9];
-    for (int q = 0; q < 9; ++q) {
-        acc[q] = cmk(0.0, 0.0);
-        int p = threadIdx.x + 256 * q;
-        pc[q] = pd[q] = -1;
-        if (q < np && p < P) {
-            // p -> (c, d) with c <= d, row-major over the upper triangle
-            int c = 0, rem = p;
-            while (rem >= Nv - c) { rem -= Nv - c; ++c; }
-            pc[q] = c;
-            pd[q] = c + rem;
-        }
-    }
-    for (int k0 = 0; k0 < K; k0 += GCH) {
-        __syncthreads();
-        for (int e = threadIdx.x; e < Nv * GCH; e += 256) {
-            int c = e / GCH, kk = e % GCH;
-            sh[c * (GCH + 1) + kk] = (k0 + kk < K) ? W[(size_t)c * K + k0 + kk] : make_double2(0.0, 0.0);
-        }
-        __syncthreads();
-        for (int q = 0; q < 9; ++q) {
-            if (pc[q] < 0) continue;
-            const double2* a = sh + pc[q] * (GCH + 1);
-            const double2* b = sh + pd[q] * (GCH + 1);
-            for (int kk = 0; kk < GCH; ++kk)
-                cjmac(acc[q], cmk(a[kk].x, a[kk].y), cmk(b[kk].x, b[kk].y));
-        }
-    }
-    for (int q = 0; q < 9; ++q)
-        if (pc[q] >= 0) G[((size_t)ya * Nv + pc[q]) * Nv + pd[q]] = make_double2(acc[q].re, acc[q].im);
-}
-
-// In place: G (upper) -> R with G = R^+ R; then Rinv = R^{-1} (upper).
-__global__ void k_chol_inv(int Nv, double2* __restrict__ G, double2* __restrict__ Rinv, double tol, int* bad) {
-    const int ya = blockIdx.x;
-    double2* R = G + (size_t)ya * Nv * Nv;
+    extern __shared__ double2 R[];
+    for (int e = threadIdx.x; e < Nv * Nv; e += blockDim.x) R[e] = G[(size_t)ya * Nv * Nv + e];
+    __syncthreads();
     double2* X = Rinv + (size_t)ya * Nv * Nv;
     __shared__ double diag;
     for (int j = 0; j < Nv; ++j) {
@@ -122,47 +232,6 @@ __global__ void k_chol_inv(int Nv, double2* __restrict__ G, double2* __restrict_
     }
 }
 
-// In place: w_d <- sum_{c<=d} w_c Rinv[c][d], d processed from the top down.
-// (B32 / B16 non-null: the result is also written in FP32 and FP16, the
-// copies the transfers read)
-__global__ __launch_bounds__(256) void k_apply_rinv(double2* __restrict__ B, int Nv, int K,
-                                                    const double2* __restrict__ Rinv, float2* __restrict__ B32,
-                                                    __half2* __restrict__ B16) {
-    const int ya = blockIdx.x;
-    double2* W = B + (size_t)ya * Nv * K;
-    const double2* X = Rinv + (size_t)ya * Nv * Nv;
-    extern __shared__ double2 xs[];   // Nv*Nv
-    for (int e = threadIdx.x; e < Nv * Nv; e += blockDim.x) xs[e] = X[e];
-    __syncthreads();
-    for (int k = threadIdx.x; k < K; k += blockDim.x) {
-        for (int d1 = Nv; d1 > 0; d1 -= 16) {
-            int d0 = d1 - 16 < 0 ? 0 : d1 - 16;
-            cx<double> acc[16];
-            for (int q = 0; q < 16; ++q) acc[q] = cmk(0.0, 0.0);
-            for (int c = 0; c < d1; ++c) {
-                double2 w = W[(size_t)c * K + k];
-                cx<double> wc = cmk(w.x, w.y);
-#pragma unroll
-                for (int q = 0; q < 16; ++q) {
-                    int d = d0 + q;
-                    if (d < d1 && c <= d) {
-                        double2 x = xs[c * Nv + d];
-                        cmac(acc[q], wc, cmk(x.x, x.y));
-                    }
-                }
-            }
-            for (int q = 0; q < 16; ++q)
-                if (d0 + q < d1) {
-                    const size_t o = (size_t)(d0 + q) * K + k;
-                    W[o] = make_double2(acc[q].re, acc[q].im);
-                    const size_t og = (size_t)ya * Nv * K + o;
-                    if (B32) B32[og] = make_float2((float)acc[q].re, (float)acc[q].im);
-                    if (B16) B16[og] = __floats2half2_rn((float)acc[q].re, (float)acc[q].im);
-                }
-        }
-    }
-}
-
 // ---------------------------------------------------------------------------
 // restrict / prolong
 // ---------------------------------------------------------------------------
@@ -172,13 +241,6 @@ __global__ __launch_bounds__(256) void k_apply_rinv(double2* __restrict__ B, int
 // matrix cores (16x16x4) so that each basis and field entry is loaded once, in
 // the lane that multiplies it; they are bound by memory.
 
-// field offset of column k: s'col V + l
-__device__ __forceinline__ size_t col_off(int k, int Vb, size_t V) {
-    int s = 0;
-#pragma unroll
-    for (int m = 1; m < 6; ++m) s += k >= m * Vb;
-    return (size_t)s * (V - Vb) + (uint32_t)k;
-}
 template <typename S, typename R> __device__ __forceinline__ void ld1c(const S* p, R& re, R& im) {
     const cx<R> v = ldc<S, R>(p);
     re = v.re;
@@ -626,25 +688,20 @@ __global__ __launch_bounds__(256) void k_coarse_gamma_mfma(Geo g, int Nv, const 
 // ---------------------------------------------------------------------------
 // ABI: build the subspace
 // ---------------------------------------------------------------------------
-static int cholqr_pass(mglma_ctx* c, double2* Gb, double2* Rb, int* bad, bool copies) {
-    const Geo& g = c->geo;
-    const int Nv = c->Nv, K = 6 * g.Vb;
-    const int nya = g.V1 * 2;
-    size_t sh = (size_t)Nv * (GCH + 1) * sizeof(double2);
-    hipLaunchKernelGGL(k_gram, dim3(nya), dim3(256), sh, c->stream, c->B64, Nv, K, Gb);
-    HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_chol_inv, dim3(nya), dim3(64), 0, c->stream, Nv, Gb, Rb, 3e-7, bad);
-    HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_apply_rinv, dim3(nya), dim3(256), (size_t)Nv * Nv * sizeof(double2), c->stream, c->B64, Nv,
-                       K, (const double2*)Rb, copies ? c->B32 : nullptr, copies ? c->B16 : nullptr);
+template <int NTR, bool APPLY, bool GRAM, bool TV>
+static int qr_pass(mglma_ctx* c, double2* B, int nsets, int Nv, int K, const double2* tv, const double2* X, double2* G,
+                   float2* B32, __half2* B16) {
+    const size_t shb = ((APPLY ? 2 * NTR * (NTR + 1) * 64 : 0) + (GRAM ? 4 * NTR * 256 : 0)) * sizeof(double2);
+    hipLaunchKernelGGL((k_qr_pass<NTR, APPLY, GRAM, TV>), dim3(nsets), dim3(256), shb, c->stream, c->geo, Nv, K, tv, B,
+                       X, G, B32, B16);
     HIP_TRY(hipGetLastError());
     return MGLMA_OK;
 }
 
-// Cholesky QR, twice, of nsets sets of Nv vectors of K complex each (B
-// [nsets][Nv][K], in place, FP64): each set orthonormalised in order with a
-// positive real diagonal.  Errors: RANK.
-int mg_cholqr_sets(mglma_ctx* c, double2* B, int nsets, int Nv, int K) {
+// Cholesky QR twice, B [nsets][Nv][K]: Gram of the source; apply and Gram of the
+// result; apply.  TV: the source is the test vectors, else B itself.
+template <int NTR, bool TV>
+static int cholqr(mglma_ctx* c, double2* B, int nsets, int Nv, int K, const double2* tv, float2* B32, __half2* B16) {
     const size_t gsz = (size_t)nsets * Nv * Nv * sizeof(double2);
     double2 *Gb, *Rb;
     int* bad;
@@ -652,18 +709,33 @@ int mg_cholqr_sets(mglma_ctx* c, double2* B, int nsets, int Nv, int K) {
     MG_TRY(mg_scratch(c, 1, gsz, (void**)&Rb));
     MG_TRY(mg_scratch(c, 7, 64, (void**)&bad));
     HIP_TRY(hipMemsetAsync(bad, 0, sizeof(int), c->stream));
-    for (int pass = 0; pass < 2; ++pass) {
-        const size_t sh = (size_t)Nv * (GCH + 1) * sizeof(double2);
-        hipLaunchKernelGGL(k_gram, dim3(nsets), dim3(256), sh, c->stream, B, Nv, K, Gb);
-        hipLaunchKernelGGL(k_chol_inv, dim3(nsets), dim3(64), 0, c->stream, Nv, Gb, Rb, 3e-7, bad);
-        hipLaunchKernelGGL(k_apply_rinv, dim3(nsets), dim3(256), (size_t)Nv * Nv * sizeof(double2), c->stream, B, Nv,
-                           K, (const double2*)Rb, (float2*)nullptr, (__half2*)nullptr);
-        HIP_TRY(hipGetLastError());
-    }
+    const size_t shr = (size_t)Nv * Nv * sizeof(double2);
+    MG_TRY((qr_pass<NTR, false, true, TV>(c, B, nsets, Nv, K, tv, nullptr, Gb, nullptr, nullptr)));
+    hipLaunchKernelGGL(k_chol_inv, dim3(nsets), dim3(64), shr, c->stream, Nv, (const double2*)Gb, Rb, 3e-7, bad);
+    MG_TRY((qr_pass<NTR, true, true, TV>(c, B, nsets, Nv, K, tv, Rb, Gb, nullptr, nullptr)));
+    hipLaunchKernelGGL(k_chol_inv, dim3(nsets), dim3(64), shr, c->stream, Nv, (const double2*)Gb, Rb, 3e-7, bad);
+    MG_TRY((qr_pass<NTR, true, false, false>(c, B, nsets, Nv, K, nullptr, Rb, nullptr, B32, B16)));
     int hbad = 0;
     HIP_TRY(hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     return hbad ? MGLMA_ERR_RANK : MGLMA_OK;
+}
+template <bool TV>
+static int cholqr_n(mglma_ctx* c, double2* B, int nsets, int Nv, int K, const double2* tv, float2* B32, __half2* B16) {
+    switch ((Nv + 15) / 16) {
+        case 1: return cholqr<1, TV>(c, B, nsets, Nv, K, tv, B32, B16);
+        case 2: return cholqr<2, TV>(c, B, nsets, Nv, K, tv, B32, B16);
+        case 3: return cholqr<3, TV>(c, B, nsets, Nv, K, tv, B32, B16);
+        case 4: return cholqr<4, TV>(c, B, nsets, Nv, K, tv, B32, B16);
+        default: return MGLMA_ERR_SHAPE;
+    }
+}
+
+// Cholesky QR, twice, of nsets sets of Nv vectors of K complex each (B
+// [nsets][Nv][K], in place, FP64): each set orthonormalised in order with a
+// positive real diagonal.  Errors: RANK.
+int mg_cholqr_sets(mglma_ctx* c, double2* B, int nsets, int Nv, int K) {
+    return cholqr_n<false>(c, B, nsets, Nv, K, nullptr, nullptr, nullptr);
 }
 
 extern "C" int mglma_build_subspace(mglma_ctx* c, int Nv, const double* tv) {
@@ -686,26 +758,13 @@ extern "C" int mglma_build_subspace(mglma_ctx* c, int Nv, const double* tv) {
     MG_TRY(mg_malloc(c, (void**)&c->Dbf, nd * 4));
     MG_TRY(mg_malloc(c, (void**)&c->G1, (size_t)g.V1 * g.b[0] * 3 * Nv * Nv * 16));
 
-    // 1. block-project and chirally split the test vectors
-    hipLaunchKernelGGL(k_tv_to_basis, dim3((g.V + 255) / 256, Nv), dim3(256), 0, c->stream, g, Nv,
-                       (const double2*)tv, c->B64);
-    HIP_TRY(hipGetLastError());
-    // 2. orthonormalise each (block, chirality) set: Cholesky QR twice
-    size_t gsz = (size_t)g.V1 * 2 * Nv * Nv * sizeof(double2);
-    double2 *Gb, *Rb;
-    int* bad;
-    MG_TRY(mg_scratch(c, 0, gsz, (void**)&Gb));
-    MG_TRY(mg_scratch(c, 1, gsz, (void**)&Rb));
-    MG_TRY(mg_scratch(c, 7, 64, (void**)&bad));
-    HIP_TRY(hipMemsetAsync(bad, 0, sizeof(int), c->stream));
-    MG_TRY(cholqr_pass(c, Gb, Rb, bad, false));
-    int hbad = 0;
-    HIP_TRY(hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    if (hbad) { mg_free_subspace(c); return MGLMA_ERR_RANK; }
-    MG_TRY(cholqr_pass(c, Gb, Rb, bad, true));   // also writes the FP16 copy
+    // 1. block-project and chirally split the test vectors and orthonormalise
+    //    each (block, chirality) set: Cholesky QR twice (also writes the FP16 copy)
+    const int qrc = cholqr_n<true>(c, c->B64, g.V1 * 2, Nv, 6 * g.Vb, (const double2*)tv, c->B32, c->B16);
+    if (qrc == MGLMA_ERR_RANK) mg_free_subspace(c);
+    MG_TRY(qrc);
 
-    // 3. Galerkin operator, block by block; the forward pieces go to a
+    // 2. Galerkin operator, block by block; the forward pieces go to a
     //    temporary of the operator's size, released after the build
     double2* gtmp;
     MG_TRY(mg_malloc(c, (void**)&gtmp, nd * 16));
@@ -715,7 +774,7 @@ extern "C" int mglma_build_subspace(mglma_ctx* c, int Nv, const double* tv) {
     mg_free(c, gtmp, nd * 16);
     if (grc != MGLMA_OK) { mg_free_subspace(c); return grc; }
 
-    // 4. coarse gamma matrices
+    // 3. coarse gamma matrices
     if ((g.Vb / g.b[0]) % 4 == 0 && Nv <= 32)
         hipLaunchKernelGGL(k_coarse_gamma_mfma, dim3(g.V1 * g.b[0]), dim3(256), (size_t)4 * Nv * Nv * sizeof(double2),
                            c->stream, g, Nv, c->B64, c->G1);
@@ -724,7 +783,7 @@ extern "C" int mglma_build_subspace(mglma_ctx* c, int Nv, const double* tv) {
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(c->stream));
 
-    // 5. even-odd reduced form of D_1 where the coarse lattice allows it
+    // 4. even-odd reduced form of D_1 where the coarse lattice allows it
     MG_TRY(mg_eo_setup(c));
     c->have_subspace = true;
     return MGLMA_OK;
