@@ -123,46 +123,85 @@ __global__ __launch_bounds__(256) void k_inv_self(const double2* __restrict__ D,
     }
 }
 
-// H[y][d] = D_yy^{-1} D[y][1 + d] (d < 8), FP64 products rounded to bfloat16,
-// planar [y][d][re/im][i][j].  One workgroup per site: D_yy^{-1} staged in LDS
-// once for the eight products; thread t owns column j = t % nc and the rows
-// i = g, g + G, ... (g = t / nc, G = 256 / nc groups), so each entry of D[y][d]
-// is loaded from memory once per workgroup and the inverse is read as LDS
-// broadcasts within a group.
-#define EOH_MAXR 16
+// H[y][d] = D_yy^{-1} D[y][1 + d] (d < 8), FP64 products rounded to bfloat16.
+// nc a multiple of 16: in the order in which k_coarse_hop_frag's lanes take it,
+// [y][d][row tile][chunk of 16 columns][lane (lr, lq)]{re, im}[4], row lr and
+// columns 4 lq..4 lq+3 of the tile.  Else planar [y][d][re/im][i][j].
+//
+// One workgroup per site on the FP64 matrix cores, D_yy^{-1} in LDS (rows padded
+// to an odd number of 16-byte units), wavefronts over (direction, 16 columns of
+// D[y][d]); a tile of H^T has H's columns as its rows, so that the four lanes of
+// a row of H hold four neighbouring columns after a 4 x 4 exchange.
+// 48 x 24^3, nc = 48: 0.38 ms, on the vector units 1.08.
+template <bool FULL>
 __global__ __launch_bounds__(256) void k_eo_hops(const double2* __restrict__ Dinv, const double2* __restrict__ D,
                                                  int nc, bf16_t* __restrict__ Hbf) {
-    extern __shared__ double2 Ai[];          // nc x nc
-    const int y = blockIdx.x, t = threadIdx.x, nn = nc * nc;
-    for (int e = t; e < nn; e += blockDim.x) Ai[e] = Dinv[(size_t)y * nn + e];
+    typedef Mfma<double> MF;
+    typedef MF::v4 V4;
+    extern __shared__ double2 Ai[];          // nc x ld
+    const int y = blockIdx.x, nn = nc * nc, ld = nc | 1, ntr = (nc + 15) / 16, ns = (nc + 3) / 4;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4;
+    for (int e = threadIdx.x; e < nn; e += blockDim.x) {
+        const int i = e / nc;
+        Ai[i * ld + e - i * nc] = Dinv[(size_t)y * nn + e];
+    }
     __syncthreads();
-    const int G = 256 / nc, j = t % nc, grp = t / nc;
-    if (grp >= G) return;
-    for (int d = 0; d < 8; ++d) {
+    for (int u = w; u < 8 * ntr; u += 4) {
+        const int d = u / ntr, ct = u - d * ntr;
         const double2* Bd = D + ((size_t)y * 9 + 1 + d) * nn;
-        bf16_t* out = Hbf + ((size_t)y * 8 + d) * 2 * nn;
-        for (int i0 = grp; i0 < nc; i0 += G * EOH_MAXR) {
-            double ar[EOH_MAXR], ai[EOH_MAXR];
+        const int j = 16 * ct + lr < nc ? 16 * ct + lr : nc - 1;    // columns past nc: results not written
+        double2 b[16];
 #pragma unroll
-            for (int q = 0; q < EOH_MAXR; ++q) ar[q] = ai[q] = 0.0;
-            for (int m = 0; m < nc; ++m) {
-                const double2 bv = Bd[(size_t)m * nc + j];
+        for (int s = 0; s < 16; ++s) {
+            if (s < ns) {
+                const int m = 4 * s + lq;
+                b[s] = Bd[(m < nc ? m : nc - 1) * nc + j];
+                b[s].x = m < nc ? b[s].x : 0.0;
+                b[s].y = m < nc ? b[s].y : 0.0;
+            }
+        }
+        for (int rt = 0; rt < ntr; ++rt) {
+            const double2* Ar = Ai + (16 * rt + lr < nc ? 16 * rt + lr : nc - 1) * ld;
+            V4 hr = {0, 0, 0, 0}, hi = {0, 0, 0, 0};
 #pragma unroll
-                for (int q = 0; q < EOH_MAXR; ++q) {
-                    const int i = i0 + q * G;
-                    if (i < nc) {
-                        const double2 av = Ai[i * nc + m];
-                        ar[q] = fma(av.x, bv.x, fma(-av.y, bv.y, ar[q]));
-                        ai[q] = fma(av.x, bv.y, fma(av.y, bv.x, ai[q]));
-                    }
+            for (int s = 0; s < 16; ++s) {
+                if (s < ns) {
+                    const double2 a = Ar[4 * s + lq < nc ? 4 * s + lq : nc - 1];
+                    hr = MF::mac(b[s].x, a.x, hr);
+                    hi = MF::mac(b[s].x, a.y, hi);
+                    hr = MF::mac(-b[s].y, a.y, hr);
+                    hi = MF::mac(b[s].y, a.x, hi);
                 }
             }
+            // register r: H[row 16 rt + lr][column 16 ct + lq + 4 r]
+            if constexpr (FULL) {
+                uint32_t v[4], o[4];
 #pragma unroll
-            for (int q = 0; q < EOH_MAXR; ++q) {
-                const int i = i0 + q * G;
-                if (i < nc) {
-                    out[i * nc + j] = (bf16_t)f2bf_rne((float)ar[q]);
-                    out[nn + i * nc + j] = (bf16_t)f2bf_rne((float)ai[q]);
+                for (int r = 0; r < 4; ++r)
+                    v[r] = (uint16_t)f2bf_rne((float)hr[r]) | (uint32_t)(uint16_t)f2bf_rne((float)hi[r]) << 16;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const uint32_t x = (uint32_t)__shfl((int)v[r], 16 * e + lr, 64);
+                        o[e] = r == 0 || r == lq ? x : o[e];
+                    }
+                uint4 q;
+                q.x = (o[0] & 0xffffu) | o[1] << 16;
+                q.y = (o[2] & 0xffffu) | o[3] << 16;
+                q.z = o[0] >> 16 | (o[1] & 0xffff0000u);
+                q.w = o[2] >> 16 | (o[3] & 0xffff0000u);
+                *(uint4*)(Hbf + ((((size_t)y * 8 + d) * ntr + rt) * ntr + ct) * 512 + lane * 8) = q;
+            } else {
+                bf16_t* out = Hbf + ((size_t)y * 8 + d) * 2 * nn;
+                const int i = 16 * rt + lr;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int jj = 16 * ct + MF::row(lq, r);
+                    if (i < nc && jj < nc) {
+                        out[i * nc + jj] = (bf16_t)f2bf_rne((float)hr[r]);
+                        out[nn + i * nc + jj] = (bf16_t)f2bf_rne((float)hi[r]);
+                    }
                 }
             }
         }
@@ -261,10 +300,98 @@ __global__ void k_eo_scatter(const float2* __restrict__ xe, const float2* __rest
 // H[y][d] in[n][nbr[k][d]], y = site[k] of the output parity, in the
 // compressed vectors of the other parity.  grid (Vh, ceil(nrhs/16)), block
 // 64 * ntr * DG: wave w owns row tile w % ntr and the directions d = w / ntr +
-// DG j; the DG partial sums are added in LDS in a fixed order.  FULL: nc a
-// multiple of 16.  xs may alias out (each entry is read and written by the
-// same lane).
-template <bool FULL, int DG, bool SUB>
+// DG j; the DG partial sums are added in LDS in a fixed order.  xs may alias
+// out (each entry is read and written by the same lane).
+//
+// nc a multiple of 16.  A matrix core operand has neighbouring lanes on
+// different rows, and read from row-major arrays every lane was an L1 access of
+// its own.  H therefore lies in the lanes' order (1 KB a load), and the
+// workgroup brings the eight neighbours' vectors in along their rows, rounds
+// them to bfloat16 once for all row tiles and hands them out from LDS in
+// fragment order (slots of a row of lanes exchanged against bank conflicts).
+// nc = 48: 256 sites, 20 right-hand sides 15.6 -> 7.7 us, 1296 sites, 12: 36 ->
+// 22 us (96 MB of H: 4.4 TB/s).
+template <int NTR, bool SUB>
+__global__ __launch_bounds__(256 * NTR) void k_coarse_hop_frag(int Vh, const int* __restrict__ site,
+                                                               const int* __restrict__ nbr,
+                                                               const bf16_t* __restrict__ Hbf,
+                                                               const float2* __restrict__ in, const float2* xs,
+                                                               float2* out, int nrhs) {
+    constexpr int DG = 4, nc = 16 * NTR, NTH = 256 * NTR, U = 8 * 16 * (nc / 2) / NTH;
+    __shared__ uint4 bs[8 * NTR * 64];
+    __shared__ f4_t part[2 * NTR * 64 * (DG - 1)];
+    int k, tile;
+    if (!site_tile(Vh, (nrhs + 15) / 16, &k, &tile)) return;
+    const int y = site[k], n0 = tile * 16, tid = threadIdx.x;
+    const int wall = tid >> 6, lane = tid & 63, w = wall % NTR, dg = wall / NTR;
+    const int lr = lane & 15, lq = lane >> 4;
+    // vectors: unit (direction, right-hand side, pair of columns)
+    float4 x[U];
+    int ad[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int e = u * NTH + tid, kp = e % (nc / 2), t = e / (nc / 2), n = t & 15, d = t >> 4;
+        x[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (n0 + n < nrhs) x[u] = *(const float4*)(in + ((size_t)(n0 + n) * Vh + nbr[k * 8 + d]) * nc + 2 * kp);
+        const int q = kp >> 3, l4 = (kp >> 1) & 3;
+        ad[u] = ((d * NTR + q) * 64 + l4 * 16 + (n ^ (4 * l4))) * 4 + (kp & 1);
+    }
+    uint4 a[2][NTR];
+#pragma unroll
+    for (int jd = 0; jd < 2; ++jd)
+#pragma unroll
+        for (int q = 0; q < NTR; ++q)
+            a[jd][q] = *(const uint4*)(Hbf + ((((size_t)y * 8 + dg + DG * jd) * NTR + w) * NTR + q) * 512 + lane * 8);
+    uint32_t* bw = (uint32_t*)bs;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        bw[ad[u]] = (uint16_t)f2bf_rne(x[u].x) | (uint32_t)(uint16_t)f2bf_rne(x[u].z) << 16;
+        bw[ad[u] + 2] = (uint16_t)f2bf_rne(x[u].y) | (uint32_t)(uint16_t)f2bf_rne(x[u].w) << 16;
+    }
+    __syncthreads();
+    f4_t cr = {0.f, 0.f, 0.f, 0.f}, ci = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int jd = 0; jd < 2; ++jd)
+#pragma unroll
+        for (int q = 0; q < NTR; ++q) {
+            const uint4 b = bs[((dg + DG * jd) * NTR + q) * 64 + lq * 16 + (lr ^ (4 * lq))], h = a[jd][q];
+            const bf4_t ar = __builtin_bit_cast(bf4_t, make_uint2(h.x, h.y));
+            const bf4_t ai = __builtin_bit_cast(bf4_t, make_uint2(h.z, h.w));
+            const bf4_t br = __builtin_bit_cast(bf4_t, make_uint2(b.x, b.y));
+            const bf4_t bi = __builtin_bit_cast(bf4_t, make_uint2(b.z, b.w));
+            const bf4_t bn = __builtin_bit_cast(bf4_t, make_uint2(b.z ^ 0x80008000u, b.w ^ 0x80008000u));
+            cr = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ar, br, cr, 0, 0, 0);
+            cr = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ai, bn, cr, 0, 0, 0);
+            ci = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ar, bi, ci, 0, 0, 0);
+            ci = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ai, br, ci, 0, 0, 0);
+        }
+    if (dg > 0) {
+        part[((dg - 1) * NTR + w) * 2 * 64 + lane] = cr;
+        part[((dg - 1) * NTR + w) * 2 * 64 + 64 + lane] = ci;
+    }
+    __syncthreads();
+    if (dg > 0) return;
+#pragma unroll
+    for (int q = 1; q < DG; ++q) {
+        cr += part[((q - 1) * NTR + w) * 2 * 64 + lane];
+        ci += part[((q - 1) * NTR + w) * 2 * 64 + 64 + lane];
+    }
+    // C[row = 4*lq + t][col = lr]
+    if (n0 + lr < nrhs) {
+        const size_t ob = ((size_t)(n0 + lr) * Vh + k) * nc + 16 * w + 4 * lq;
+        float4 v0 = make_float4(cr[0], ci[0], cr[1], ci[1]), v1 = make_float4(cr[2], ci[2], cr[3], ci[3]);
+        if (SUB) {
+            const float4 x0 = *(const float4*)(xs + ob), x1 = *(const float4*)(xs + ob + 2);
+            v0 = make_float4(x0.x - v0.x, x0.y - v0.y, x0.z - v0.z, x0.w - v0.w);
+            v1 = make_float4(x1.x - v1.x, x1.y - v1.y, x1.z - v1.z, x1.w - v1.w);
+        }
+        *(float4*)(out + ob) = v0;
+        *(float4*)(out + ob + 2) = v1;
+    }
+}
+
+// any nc, H planar
+template <int DG, bool SUB>
 __global__ void k_coarse_hop_bf16(int nc, int Vh, const int* __restrict__ site, const int* __restrict__ nbr,
                                   const bf16_t* __restrict__ Hbf, const float2* __restrict__ in, const float2* xs,
                                   float2* out, int nrhs) {
@@ -291,27 +418,16 @@ __global__ void k_coarse_hop_bf16(int nc, int Vh, const int* __restrict__ site, 
         for (int k0 = 0; k0 < nc; k0 += 16) {
             const int kb = k0 + 4 * lq;
             bf4_t ar, ai, br, bi, bn;
-            if (FULL) {
-                ar = *(const bf4_t*)(Dr + (size_t)m * nc + kb);
-                ai = *(const bf4_t*)(Di + (size_t)m * nc + kb);
-                float4 x01 = nok ? *(const float4*)(v + kb) : make_float4(0.f, 0.f, 0.f, 0.f);
-                float4 x23 = nok ? *(const float4*)(v + kb + 2) : make_float4(0.f, 0.f, 0.f, 0.f);
-                br[0] = f2bf_rne(x01.x); bi[0] = f2bf_rne(x01.y); bn[0] = f2bf_rne(-x01.y);
-                br[1] = f2bf_rne(x01.z); bi[1] = f2bf_rne(x01.w); bn[1] = f2bf_rne(-x01.w);
-                br[2] = f2bf_rne(x23.x); bi[2] = f2bf_rne(x23.y); bn[2] = f2bf_rne(-x23.y);
-                br[3] = f2bf_rne(x23.z); bi[3] = f2bf_rne(x23.w); bn[3] = f2bf_rne(-x23.w);
-            } else {
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const int kk = kb + t;
-                    const bool ok = kk < nc;
-                    ar[t] = (ok && m < nc) ? (short)Dr[(size_t)m * nc + kk] : (short)0;
-                    ai[t] = (ok && m < nc) ? (short)Di[(size_t)m * nc + kk] : (short)0;
-                    const float2 x = (ok && nok) ? v[kk] : make_float2(0.f, 0.f);
-                    br[t] = f2bf_rne(x.x);
-                    bi[t] = f2bf_rne(x.y);
-                    bn[t] = f2bf_rne(-x.y);
-                }
+            for (int t = 0; t < 4; ++t) {
+                const int kk = kb + t;
+                const bool ok = kk < nc;
+                ar[t] = (ok && m < nc) ? (short)Dr[(size_t)m * nc + kk] : (short)0;
+                ai[t] = (ok && m < nc) ? (short)Di[(size_t)m * nc + kk] : (short)0;
+                const float2 x = (ok && nok) ? v[kk] : make_float2(0.f, 0.f);
+                br[t] = f2bf_rne(x.x);
+                bi[t] = f2bf_rne(x.y);
+                bn[t] = f2bf_rne(-x.y);
             }
             cr = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ar, br, cr, 0, 0, 0);
             cr = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ai, bn, cr, 0, 0, 0);
@@ -598,7 +714,11 @@ int mg_eo_setup(mglma_ctx* c) {
     hipLaunchKernelGGL(k_inv_self, dim3(V1), dim3(256), nn * sizeof(double2), c->stream, c->D64, nc, Dinv,
                        c->eo_Dinv32, bad);
     HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_eo_hops, dim3(V1), dim3(256), nn * sizeof(double2), c->stream, Dinv, c->D64, nc, c->eo_Hbf);
+    const size_t shh = (size_t)nc * (nc | 1) * sizeof(double2);
+    if (nc % 16 == 0)
+        hipLaunchKernelGGL(k_eo_hops<true>, dim3(V1), dim3(256), shh, c->stream, Dinv, c->D64, nc, c->eo_Hbf);
+    else
+        hipLaunchKernelGGL(k_eo_hops<false>, dim3(V1), dim3(256), shh, c->stream, Dinv, c->D64, nc, c->eo_Hbf);
     HIP_TRY(hipGetLastError());
     int hbad = 0;
     HIP_TRY(hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, c->stream));
@@ -663,15 +783,25 @@ int mg_eo_hop(mglma_ctx* c, int po, const void* in, const void* xs, void* out, i
     const int* nbr = c->eo_nbr + (size_t)po * Vh * 8;
     constexpr int DG = 4;
     dim3 grid(site_tile_grid(Vh, (nrhs + 15) / 16)), block(64 * ntr * DG);
-    const bool full = nc % 16 == 0;
-#define HOP_LAUNCH(F, S)                                                                                     \
-    hipLaunchKernelGGL((k_coarse_hop_bf16<F, DG, S>), grid, block, 0, c->stream, nc, Vh, site, nbr, c->eo_Hbf, \
+#define HOP_FRAG(N, S)                                                                                       \
+    hipLaunchKernelGGL((k_coarse_hop_frag<N, S>), grid, block, 0, c->stream, Vh, site, nbr, c->eo_Hbf,       \
                        (const float2*)in, (const float2*)xs, (float2*)out, nrhs)
-    if (xs) {
-        if (full) HOP_LAUNCH(true, true); else HOP_LAUNCH(false, true);
-    } else {
-        if (full) HOP_LAUNCH(true, false); else HOP_LAUNCH(false, false);
+#define HOP_LAUNCH(S)                                                                                        \
+    switch (nc % 16 == 0 ? ntr : 0) {                                                                        \
+        case 1: HOP_FRAG(1, S); break;                                                                       \
+        case 2: HOP_FRAG(2, S); break;                                                                       \
+        case 3: HOP_FRAG(3, S); break;                                                                       \
+        case 4: HOP_FRAG(4, S); break;                                                                       \
+        default:                                                                                             \
+            hipLaunchKernelGGL((k_coarse_hop_bf16<DG, S>), grid, block, 0, c->stream, nc, Vh, site, nbr, c->eo_Hbf, \
+                               (const float2*)in, (const float2*)xs, (float2*)out, nrhs);                    \
     }
+    if (xs) {
+        HOP_LAUNCH(true)
+    } else {
+        HOP_LAUNCH(false)
+    }
+#undef HOP_FRAG
 #undef HOP_LAUNCH
     HIP_TRY(hipGetLastError());
     return MGLMA_OK;

@@ -309,7 +309,7 @@ struct mglma_ctx {
     int* eo_site = nullptr;        // [2][Vh] coarse site of compressed index k, increasing y
     int* eo_nbr = nullptr;         // [2][Vh][8] compressed index of neighbour dir 1+d (other parity)
     float* eo_Dinv32 = nullptr;    // [V1][re/im][nc][nc] inverse self blocks, FP32 planar
-    bf16_t* eo_Hbf = nullptr;      // [V1][8][2][nc][nc] D_yy^{-1} D_y,dir planar bfloat16
+    bf16_t* eo_Hbf = nullptr;      // [V1][8][2 nc^2] D_yy^{-1} D_y,dir bfloat16 (order: k_eo_hops)
     // deflation of S with the nc constant even-site vectors Y (y_a = e_a / sqrt(Vh) on every even site)
     bool eo_defl = false, eo_defl_tried = false;
     float2* eo_SY = nullptr;       // [nc][Vh][nc] S y_a (the BF16 S of the solver)
