@@ -30,12 +30,17 @@
 // along the rows, 64 or 256 bytes a row, and changes lanes in LDS (its own
 // part of it, no barrier).  Slots are exchanged within a row (xor with the row)
 // so that neither side has bank conflicts.  FP64 takes three real products per
-// complex one (at 60 % of the cycles the matrix cores are the other bound).
-// 48 x 24^3, 24 vectors: FP64, 32 right-hand sides 417 -> 341 us (373 with four
-// products), 12: 226 -> 196, 1: 175 -> 170 (the operator's bytes); FP32, 32: 212
-// -> 193; 32 x 16^3, 20 right-hand sides FP64: 83 -> 57.  Two tiles of
-// right-hand sides a wave or a workgroup, or more loads in flight, without the
-// change of lanes: 380-430.
+// complex one (with four, the matrix cores, L1 and LDS would each be busy for as
+// long as the other two) and folds the sums of each direction into the result:
+// the error against exact values is 2.6e-15 of the result's norm (2.56e-15 with
+// four products in another order; 2.9e-15 with sums running through all nine
+// directions, three products or four).
+// 48 x 24^3, 24 vectors: FP64, 32 right-hand sides 397 -> 297 us (335 with four
+// products), 12: 226 -> 193, 1: 175 -> 170 (the operator's bytes); FP32, 32: 212
+// -> 193; 32 x 16^3, 20 right-hand sides FP64: 83 -> 52.  Tried for 32 / 20: the
+// row tiles of a site sharing vectors that the workgroup brings in once, a
+// barrier a step, 326 / 67-73; two tiles of right-hand sides a wave, 307 / 67
+// (four products) and 320 / 67 (three): fewer wavefronts cover the loads.
 template <typename R> struct CoarseTile;
 template <> struct CoarseTile<double> {
     static constexpr int LDS = 2 * 256;      // 16-byte units a wave: operator, vectors
@@ -139,7 +144,13 @@ __global__ __launch_bounds__(512) void k_coarse_mfma(Geo g, int nc, const R* __r
     const size_t V1 = g.V1, nn = (size_t)nc * nc;
     const int nk = (nc + 15) / 16, it0 = 9 * nk * dg / DG, it1 = 9 * nk * (dg + 1) / DG;
     // FP64: three real products per complex one, re = cr - ci, im = c3 - cr - ci
-    V4 cr = {0, 0, 0, 0}, ci = {0, 0, 0, 0}, c3 = {0, 0, 0, 0};
+    V4 cr = {0, 0, 0, 0}, ci = {0, 0, 0, 0}, c3 = {0, 0, 0, 0}, re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+    // FP64: the sums of one direction into those of all
+    auto flush = [&]() {
+        re += cr - ci;
+        im += c3 - cr - ci;
+        cr = ci = c3 = V4{0, 0, 0, 0};
+    };
     auto mac = [&](const R (&ar)[4], const R (&ai)[4], const R (&br)[4], const R (&bi)[4]) {
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
@@ -182,6 +193,7 @@ __global__ __launch_bounds__(512) void k_coarse_mfma(Geo g, int nc, const R* __r
             T::get(sh, lr, lq, ar, ai, br, bi);
             wave_lds_fence();
             mac(ar, ai, br, bi);
+            if (sizeof(R) == 8 && (it + 1) % nk == 0) flush();
         }
     } else {
         const size_t mo = (size_t)(m0 + lr < nc ? m0 + lr : nc - 1) * nc;
@@ -205,8 +217,8 @@ __global__ __launch_bounds__(512) void k_coarse_mfma(Geo g, int nc, const R* __r
         }
     }
     if constexpr (sizeof(R) == 8) {
-        const V4 im = c3 - cr - ci;
-        cr = cr - ci;
+        flush();
+        cr = re;
         ci = im;
     }
     if constexpr (DG > 1) {
