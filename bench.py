@@ -145,7 +145,7 @@ def measured_traffic(workload):
         return None
     rec = json.load(open(path))
     csrc = os.path.join(here, "paper_2412_06347_amd", "csrc")
-    src = b"".join(open(os.path.join(csrc, f), "rb").read() for f in ("dslash.hip", "wilson.h", "wilson_h.h"))
+    src = b"".join(open(os.path.join(csrc, f), "rb").read() for f in ("dslash.hip", "tile.h", "wilson.h", "wilson_h.h"))
     if hashlib.sha256(src).hexdigest() != rec.get("dslash_source_sha256"):
         return None
     return rec.get("f16_12rhs_hbm_bytes_per_launch")
@@ -187,7 +187,7 @@ def measured_sap_traffic(workload):
         return None
     rec = json.load(open(path))
     csrc = os.path.join(here, "paper_2412_06347_amd", "csrc")
-    src = b"".join(open(os.path.join(csrc, f), "rb").read() for f in ("sap.hip", "wilson.h", "wilson_h.h"))
+    src = b"".join(open(os.path.join(csrc, f), "rb").read() for f in ("sap.hip", "tile.h", "wilson.h", "wilson_h.h"))
     if hashlib.sha256(src).hexdigest() != rec.get("sap_source_sha256"):
         return None
     return rec.get("hbm_bytes_per_launch")
@@ -1050,7 +1050,7 @@ def main():
         "fp64_path": fp64,
         "speedup_mixed_vs_fp64": (value / fp64["solves_per_s"]) if fp64 else None,
         "dslash_GBs": dslash_gbs,
-        "roofline": {"bound": "alu", "kernel": "k_sap_half<__half2, 3> (SAP half-sweep, 12 RHS, %d block steps)" % nmr,
+        "roofline": {"bound": "alu", "kernel": "k_sap_half<__half2, h2, 4, 256, false> (SAP half-sweep, 12 RHS, %d block steps)" % nmr,
                      "achieved": ach_sap, "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": ach_sap / FP32_PEAK_TFLOPS, "traffic": traffic_sap, "avg_ms": ms_sap,
                      "peak_kind": "MI355X published FP32 vector peak",
@@ -1060,7 +1060,7 @@ def main():
                      "launches_timed": sap_launches, "avg_ms_back_to_back": ms_sap_b2b,
                      "alg_flops_per_launch": sap_flops},
         # the Wilson-clover multi-RHS apply, HBM-bound (Dslash HBM GB/s of the metric)
-        "roofline_dslash": {"bound": "hbm", "kernel": "k_dslash_h<3> (FP16 storage, FP32 sums, 12 RHS)",
+        "roofline_dslash": {"bound": "hbm", "kernel": "k_dslash_h<true> (FP16 storage, FP32 sums, 12 RHS)",
                             "achieved": dslash_gbs["f16_12rhs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                             "frac": dslash_gbs["f16_12rhs"] / HBM_PEAK_GBS, "traffic": traffic16,
                             "avg_ms": ms16, "alg_bytes_per_launch": dslash_alg_bytes(V, nr, 2)},

@@ -30,7 +30,9 @@
 // workgroup has as many threads as its block needs, not 256).  Tried: the
 // residual in a tile kernel of its own and the block solves in another, 0.49 +
 // 0.66 ms, and both kinds of workgroups interleaved in one launch over two
-// halves of the batch, 0.57 ms per half and step.
+// halves of the batch, 0.57 ms per half and step.  A grid that leaves the chip idle
+// takes 26 us a half-sweep, one wavefront's own rate of issue: links and clover
+// term kept in registers over the steps there save 5 %.
 #include "tile.h"
 #include "wilson_h.h"
 
@@ -413,8 +415,7 @@ __device__ __forceinline__ void sap_hop_res(const Geo& g, int i, int l, const in
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// The residual and the block solves of one (block, right-hand side) in one
-// kernel, for blocks of more than SAP_SPLIT sites.
+// The residual and the block solve of one (block, right-hand side).
 template <typename G, typename GP, int W, int NT, bool WRAP>
 __global__ __launch_bounds__(NT, W) void k_sap_half(Geo g, const float2* __restrict__ rhs, float2* __restrict__ z,
                                                            const G* __restrict__ U, const G* __restrict__ C,

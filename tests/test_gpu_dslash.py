@@ -126,6 +126,34 @@ def test_apply_batch_tiles(L, b, nrhs):
         assert relerr(from_dev(out), ref) < tol
 
 
+@pytest.mark.parametrize("gamma5", [0, 1])
+@pytest.mark.parametrize("L,b", [((2, 2, 2, 2), (2, 2, 2, 2)), ((4, 4, 4, 4), (4, 4, 4, 4)), ((9, 5, 3, 7), (3, 5, 3, 1))],
+                         ids=["part_of_a_tile", "whole_tiles", "tail_tile"])
+def test_apply_single_tiles(L, b, gamma5):
+    """One right-hand side: 64 sites per workgroup, a wavefront per direction,
+    with less than a tile, whole tiles and a ragged last one.  Tolerances: those
+    of test_apply_parity; FP64 and FP32 sum as a batch does."""
+    import torch
+    from paper_2412_06347_amd import mglma
+    ctx, U = _ctx(L, b, 0.124, 1.0, 0.3, seed=6)
+    D = dirac.WilsonClover(U, L, 0.124, 1.0)
+    psi = synth.gaussian_fields(2, L, seed=32)
+    ref = D.M_canon(dirac.fields_to_lattice(psi, L))
+    if gamma5:
+        ref = ref * np.array([1, 1, -1, -1]).reshape(4, 1)
+    for prec, tol in [(mglma.F64, 1e-12), (mglma.F32, 2e-6), (mglma.F16, 2e-3)]:
+        x, y, z = (ctx.fine(2, prec) for _ in range(3))
+        ctx.import_fields(to_dev(psi), x, prec)
+        for q in range(2):
+            ctx.apply_D(x[q:q + 1], y[q:q + 1], prec, gamma5)
+        ctx.apply_D(x, z, prec, gamma5)
+        out = torch.empty((2, ctx.V, 4, 3, 2), dtype=torch.float64, device="cuda")
+        ctx.export_fields(y, out, prec)
+        assert relerr(from_dev(out), ref) < tol
+        if prec != mglma.F16:
+            assert float((y - z).abs().max()) <= 8 * torch.finfo(y.dtype).eps * float(z.abs().max())
+
+
 @pytest.mark.parametrize("prec", [0, 1, 2], ids=["f64", "f32", "f16"])
 def test_apply_batch_repeats(prec):
     """A full-size batch gives the values of one right-hand side at a time in
