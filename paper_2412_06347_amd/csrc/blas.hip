@@ -150,6 +150,45 @@ __device__ __forceinline__ void write_partial(double (&v)[NV], double* lds, doub
     }
 }
 
+// Where the sums of a reduction go (the modes of k_finish).
+struct Fin {
+    double* out;
+    int mode, ostride;
+    const double* div;
+    double* aux;
+    const int* mask;
+};
+// As write_partial, but a workgroup that has a right-hand side to itself (up to
+// 256 packets) writes its results at once, the values that k_finish would make of
+// its one partial: two launches fewer per GCR step of a small coarse grid, the
+// solve of one right-hand side on 8^4 6.2 -> 5.75 ms.  (Up to four or sixteen
+// workgroups' worth in one saves nothing more there and costs 16^4 1 and 8 %.)
+template <int NV>
+__device__ __forceinline__ void write_sums(double (&v)[NV], double* lds, double* part, int nvals, const Fin& f) {
+    if (gridDim.x > 1) {
+        write_partial<NV>(v, lds, part, nvals);
+        return;
+    }
+    block_sum<NV>(v, lds);
+    if (threadIdx.x != 0) return;
+    const int r = blockIdx.y;
+    if (f.mode == 2) {
+        const double d = v[NV > 2 ? 2 : 0] + 0.0;
+        const bool on = (f.mask == nullptr || f.mask[r]) && d > 0.0;
+        f.out[2 * r] = on ? v[0] / d : 0.0;
+        f.out[2 * r + 1] = on ? v[NV > 1 ? 1 : 0] / d : 0.0;
+        if (f.aux) f.aux[r] = d;
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        if (k < nvals) {
+            const size_t o = (size_t)(k >> 1) * f.ostride + r;
+            f.out[o * 2 + (k & 1)] = f.div ? (f.div[o] > 0.0 ? v[k] / f.div[o] : 0.0) : v[k];
+        }
+    }
+}
+
 // Second pass, one workgroup per rhs: add the nb partials (each thread a
 // fixed strided share, then the same tree as above).  mode 0 writes
 // out[r][k]; mode 1 (multi-dot) writes the complex out[k / 2][ostride][r],
@@ -312,7 +351,7 @@ int mg_norm2(mglma_ctx* c, int prec, const void* x, size_t n, int nrhs, double* 
 // out[j][r] = sum_e conj(x_j[e]) y[e]   (complex, j < k <= K; out row stride ostride)
 template <typename S, int K, int C>
 __global__ __launch_bounds__(RB) void k_multidot(const S* __restrict__ x, size_t xstride, const S* __restrict__ y,
-                                                 size_t n, int k, double* part) {
+                                                 size_t n, int k, double* part, Fin f) {
     __shared__ double lds[4 * 2 * K];
     const size_t roff = (size_t)blockIdx.y * n;
     double v[2 * K];
@@ -336,7 +375,7 @@ __global__ __launch_bounds__(RB) void k_multidot(const S* __restrict__ x, size_t
             }
         }
     });
-    write_partial<2 * K>(v, lds, part, 2 * k);
+    write_sums<2 * K>(v, lds, part, 2 * k, f);
 }
 
 template <typename S>
@@ -353,8 +392,9 @@ static int multidot_t(mglma_ctx* c, const S* x, size_t xstride, int k, const S* 
         const S* xj = x + (size_t)j0 * xstride;
         double* oj = out + (size_t)j0 * nrhs * 2;
         const double* dj = div ? div + (size_t)j0 * nrhs : nullptr;
+        const Fin f = {oj, 1, nrhs, dj, nullptr, nullptr};
 #define MD_LAUNCH(KK, CC) \
-        hipLaunchKernelGGL((k_multidot<S, KK, CC>), grid, dim3(RB), 0, c->stream, xj, xstride, y, n, kk, c->red_part)
+        hipLaunchKernelGGL((k_multidot<S, KK, CC>), grid, dim3(RB), 0, c->stream, xj, xstride, y, n, kk, c->red_part, f)
         if (vec) {
             if (kk == 1) MD_LAUNCH(1, C); else if (kk <= 4) MD_LAUNCH(4, C); else MD_LAUNCH(MAXK, C);
         } else {
@@ -362,6 +402,7 @@ static int multidot_t(mglma_ctx* c, const S* x, size_t xstride, int k, const S* 
         }
 #undef MD_LAUNCH
         HIP_TRY(hipGetLastError());
+        if (nb == 1) continue;
         if (kk == 1) MG_TRY(launch_finish<2>(c, nb, nrhs, 2, oj, 1, nrhs, dj));
         else if (kk <= 4) MG_TRY(launch_finish<8>(c, nb, nrhs, 2 * kk, oj, 1, nrhs, dj));
         else MG_TRY(launch_finish<2 * MAXK>(c, nb, nrhs, 2 * kk, oj, 1, nrhs, dj));
@@ -766,7 +807,7 @@ template <typename S, typename R, int K, int C, bool TWO = true>
 __global__ __launch_bounds__(RB) void k_orth_dot(const S* __restrict__ x1, const S* __restrict__ x2, size_t xstride,
                                                  int k, const double* __restrict__ coef, S* __restrict__ y1, S* y2,
                                                  const S* y2s, const S* __restrict__ d, size_t n, int nrhs,
-                                                 double* part) {
+                                                 double* part, Fin f) {
     __shared__ double lds[4 * 3];
     const int r = blockIdx.y;
     const size_t roff = (size_t)r * n;
@@ -805,7 +846,7 @@ __global__ __launch_bounds__(RB) void k_orth_dot(const S* __restrict__ x1, const
             v[2] = fma(w[q].re, w[q].re, v[2]); v[2] = fma(w[q].im, w[q].im, v[2]);
         }
     });
-    write_partial<3>(v, lds, part, 3);
+    write_sums<3>(v, lds, part, 3, f);
 }
 
 // Chunks of MAXK directions; the first chunk reads y2 from y2s (if given),
@@ -836,13 +877,14 @@ static int multiaxpy2_t(mglma_ctx* c, const S* x1, const S* x2, size_t xstride, 
             const int nb = red_blocks(np, 1);
             MG_TRY(ensure_red(c, (size_t)nb * nrhs * 3));
             const dim3 rg(nb, nrhs);
+            const Fin f = {alpha, 2, 0, nullptr, nw2j, mask};
 #define OD_LAUNCH(KK, CC)                                                                                  \
             do if (two)                                                                                        \
                 hipLaunchKernelGGL((k_orth_dot<S, R, KK, CC, true>), rg, dim3(RB), 0, c->stream, a1, a2, xstride, kk, \
-                                   cj, y1, y2, src, d, n, nrhs, c->red_part);                                    \
+                                   cj, y1, y2, src, d, n, nrhs, c->red_part, f);                                 \
             else                                                                                               \
                 hipLaunchKernelGGL((k_orth_dot<S, R, KK, CC, false>), rg, dim3(RB), 0, c->stream, a1, a2, xstride,  \
-                                   kk, cj, y1, y2, src, d, n, nrhs, c->red_part); while (0)
+                                   kk, cj, y1, y2, src, d, n, nrhs, c->red_part, f); while (0)
             if (vec) {
                 if (kk <= 0) OD_LAUNCH(1, C); else if (kk <= 4) OD_LAUNCH(4, C); else OD_LAUNCH(MAXK, C);
             } else {
@@ -850,7 +892,7 @@ static int multiaxpy2_t(mglma_ctx* c, const S* x1, const S* x2, size_t xstride, 
             }
 #undef OD_LAUNCH
             HIP_TRY(hipGetLastError());
-            MG_TRY(launch_finish<3>(c, nb, nrhs, 3, alpha, 2, 0, nullptr, nw2j, mask));
+            if (nb > 1) MG_TRY(launch_finish<3>(c, nb, nrhs, 3, alpha, 2, 0, nullptr, nw2j, mask));
         } else {
 #define M2_LAUNCH(KK, CC) \
             do if (two) \

@@ -154,6 +154,24 @@ def test_coarse_solve_deflated(pair):
     assert (np.linalg.norm(r.reshape(2, -1), axis=1) / np.linalg.norm(b.reshape(2, -1), axis=1)).max() <= 1e-10
 
 
+@pytest.mark.parametrize("Nv,nrhs", [(16, 1), (16, 5), (17, 2), (32, 3)])
+def test_coarse_solve_reduction_edges(Nv, nrhs):
+    """The sums of a GCR step around one workgroup per right-hand side (256
+    packets of two complex numbers on 16 sites of a parity): exactly one, the
+    first size past it, and two full ones.  The residual asked for, checked with
+    the oracle's stencil."""
+    import torch
+    from paper_2412_06347_amd import mglma
+    p = Pair((8, 4, 4, 4), (2, 2, 2, 2), Nv, seed=21)
+    b = synth.gaussian_coarse(nrhs, p.bl.V1, 2 * Nv, 22)
+    x = torch.zeros((nrhs, p.bl.V1, 2 * Nv, 2), dtype=torch.float64, device="cuda")
+    prm = mglma.default_params(inner=mglma.F32, coarse=mglma.BF16, tol=1e-10, coarse_eo=1)
+    p.ctx.coarse_solve(to_dev(b), x, prm)
+    r = b - coarse.coarse_apply(p.D1, p.nbr, from_dev(x))
+    rel = np.linalg.norm(r.reshape(nrhs, -1), axis=1) / np.linalg.norm(b.reshape(nrhs, -1), axis=1)
+    assert rel.max() < 1e-9
+
+
 def test_fine_solve_even_odd(pair):
     """The MG-preconditioned fine solve with the even-odd coarse GCR reaches
     1e-10 in the oracle's FP64 residual, in no more inner iterations than
