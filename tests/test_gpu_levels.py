@@ -101,6 +101,29 @@ def test_levels_point_time_average(pair):
     assert relerr(np.mean(one, axis=0), ref[0] + ref[1] + ref[2]) < 1e-12
 
 
+@pytest.mark.parametrize("same", [True, False])
+@pytest.mark.parametrize("L", [(2, 4, 4, 4), (4, 8, 4, 8), (2, 16, 8, 8)], ids=["part_of_a_pass", "one_chunk", "chunks"])
+def test_fine_slices_sum_sites_first(L, same):
+    """One colour pair of every site adds up to 16, each of the other eight to
+    16 a^2 = 2^-48 in four equal parts that are a quarter of 16's spacing: a sum
+    that carries the 16 along drops all of them (2^-49 of the result = 16 u, u =
+    2^-53), sums of each colour pair first are exact, as are sums over equal sites
+    and a power of two of them.  What remains is the factor 1/3 and its product:
+    at most 2 u, and 1 u of the expected value."""
+    from paper_2412_06347_amd import mglma
+    a = 2.0 ** -26
+    psi = np.full((4, 3, int(np.prod(L)), 4, 3), a, dtype=complex)
+    psi[:, 0, :, :, 0] = 1.0
+    ctx = mglma.Context(L, (2, 2, 2, 2), 0.12, 1.0)
+    x, y = ctx.fine(12), ctx.fine(12)
+    for f in (x, y):
+        ctx.import_fields(to_dev(psi.reshape(12, -1, 4, 3)), f)
+    V3 = int(np.prod(L[1:]))
+    got = ctx.contract_pair(POINT, [0], x, x if same else y)
+    ref = V3 * (16 * (1 + 8 * a * a)) / 3
+    assert np.abs(np.abs(got) - ref).max() <= 4 * 2.0 ** -53 * ref
+
+
 def test_contract_pair_cross_terms(pair):
     """Source mean of eq:C_stoch2 for two different pieces (i != j), fine and
     coarse route, against the oracle."""
