@@ -177,7 +177,7 @@ __global__ __launch_bounds__(256, W) void k_dslash_tile(Geo g, const S* __restri
             for (int k = 0; k < 6; ++k) {
                 cx<R> v = res[k] - kappa * acc[6 * ch + k];
                 if (gamma5 && ch == 1) v = -v;
-                if (RESID) v = isc * (buf_ldc<S, R>(comp_rsrc(rsub + q * 12 * V, 6 * ch + k, 1, vc), io, 0) - v);
+                if (RESID) v = isc * (buf_ldc<S, R>(comp_rsrc<1>(rsub + q * 12 * V, 6 * ch + k, vc), io, 0) - v);
                 buf_stc<SO, R>(out + q * 12 * V, vc, io, 6 * ch + k, v);
             }
         }
@@ -273,7 +273,8 @@ __global__ __launch_bounds__(256, 4) void k_dslash_h(Geo g, const h2* __restrict
                 res[0][k] = -kappa * acc[6 * ch + k];
             }
             clover_dot2<1>([&](int k) { return CL ? ul[(72 + ch * 18 + k) * TILE + lo]
-                                                  : buf_ld<h2>(comp_rsrc(C, ch * 18 + k / 3 * 3, 3, V), io, k % 3 * V * 4u); },
+                                                  : buf_ld<h2>(comp_rsrc<TILE_COMPS>(C, ch * 18 + k / TILE_COMPS * TILE_COMPS, V),
+                                                               io, k % TILE_COMPS * V * 4u); },
                            p, res);
 #pragma unroll
             for (int k = 0; k < 6; ++k) {

@@ -68,7 +68,7 @@ template <typename G, typename F>
 __device__ __forceinline__ void block_links(const G* __restrict__ U, int mu, uint32_t V, uint32_t site, F use) {
     rsrc_t r[3];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) r[a] = comp_rsrc(U, mu * 9 + 3 * a, 3, V);
+    for (int a = 0; a < 3; ++a) r[a] = comp_rsrc<SAP_COMPS>(U, mu * 9 + 3 * a, V);
 #pragma unroll
     for (int e = 0; e < 9; ++e) use(e, buf_ld<G>(r[e / 3], site * (uint32_t)sizeof(G), e % 3 * V * (uint32_t)sizeof(G)));
 }
@@ -300,14 +300,14 @@ __device__ __forceinline__ void sap_block_solve(const Geo& g, uint32_t lo, int l
                     own[0][k] = 6 * ch + k == 5 ? sh[5 * LD + lt] : to_h2(isc * s[6 * ch + k]);
                     res[0][k] = -kappa * t[6 * ch + k];
                 }
-                clover_dot2<1>([&](int k) { return buf_ld<h2>(comp_rsrc(C, ch * 18 + k / 3 * 3, 3, V), io * 4u,
+                clover_dot2<1>([&](int k) { return buf_ld<h2>(comp_rsrc<SAP_COMPS>(C, ch * 18 + k / 3 * 3, V), io * 4u,
                                                               k % 3 * V * 4u); },
                                own, res);
 #pragma unroll
                 for (int k = 0; k < 6; ++k) t[6 * ch + k] = sig * res[0][k];
             } else {
                 cx<float> res[6];
-                clover_apply<float>([&](int k) { return buf_ldc<G, float>(comp_rsrc(C, ch * 18 + k / 3 * 3, 3, V), io,
+                clover_apply<float>([&](int k) { return buf_ldc<G, float>(comp_rsrc<SAP_COMPS>(C, ch * 18 + k / 3 * 3, V), io,
                                                                           k % 3 * V); },
                                     s + 6 * ch, res);
 #pragma unroll
@@ -398,7 +398,7 @@ __device__ __forceinline__ void sap_hop_res(const Geo& g, int i, int l, const in
     for (int k = 0; k < 6; ++k) o[k] = cmk(0.f, 0.f);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const rsrc_t ru = comp_rsrc(U, MU * 9 + 3 * a, 3, V);
+        const rsrc_t ru = comp_rsrc<SAP_COMPS>(U, MU * 9 + 3 * a, V);
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
             const G w = buf_ld<G>(ru, us, b * V * (uint32_t)sizeof(G));
@@ -539,6 +539,7 @@ int mg_sap(mglma_ctx* c, int prec, const void* r, void* z, int nrhs, int ncycle,
     if (nrhs == 0 || ncycle == 0) return MGLMA_OK;
     MG_TRY(mg_sap_setup(c));
     const Geo& g = c->geo;
+    if (!sap_fits(g.V)) return MGLMA_ERR_SHAPE;   // 179 million sites: links and clover term are 361 GB there
     for (int h = 0; h < 2 * ncycle; ++h) {
         const int nblk = h % 2 == 0 ? c->sap_n0 : g.V1 - c->sap_n0;
         if (nblk == 0) continue;

@@ -73,7 +73,10 @@ __device__ __forceinline__ int opaque_zero() {
 }
 // Buffer loads and stores: the per-component offset (component x V) is uniform
 // and goes in a scalar register, the site offset is the only vector operand.
-// A resource spans a few components, so that its bytes stay below 2^32 (tile_fits).
+// A resource's bytes stay below 2^32: it spans at most TILE_COMPS components of
+// the fields, links and clover term here, SAP_COMPS in the SAP kernel, and larger
+// lattices take another path (tile_fits) or are refused (sap_fits).
+constexpr int TILE_COMPS = 2, SAP_COMPS = 3;
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 __device__ __forceinline__ rsrc_t mk_rsrc(const void* p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
@@ -98,19 +101,21 @@ template <typename S> __device__ __forceinline__ void buf_st(S* f, uint32_t V, u
     else if constexpr (sizeof(S) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2_t, v), r, off, 0, 0);
     else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4_t, v), r, off, 0, 0);
 }
-// components [c0, c0 + n) of a field
-template <typename S> __device__ __forceinline__ rsrc_t comp_rsrc(S* f, int c0, int n, uint32_t V) {
-    return mk_rsrc(f + (size_t)c0 * V, (uint32_t)n * V * (uint32_t)sizeof(S));
+// components [c0, c0 + n) of a field (n: 1, TILE_COMPS or SAP_COMPS)
+template <int n, typename S> __device__ __forceinline__ rsrc_t comp_rsrc(S* f, int c0, uint32_t V) {
+    return mk_rsrc(f + (size_t)c0 * V, n * V * (uint32_t)sizeof(S));
 }
-// one right-hand side, two components a resource
+// one right-hand side
 struct FieldRsrc {
     rsrc_t part[6];
 };
 template <typename S> __device__ __forceinline__ FieldRsrc field_rsrc(S* f, uint32_t V) {
-    return {{comp_rsrc(f, 0, 2, V), comp_rsrc(f, 2, 2, V), comp_rsrc(f, 4, 2, V), comp_rsrc(f, 6, 2, V),
-             comp_rsrc(f, 8, 2, V), comp_rsrc(f, 10, 2, V)}};
+    return {{comp_rsrc<TILE_COMPS>(f, 0, V), comp_rsrc<TILE_COMPS>(f, 2, V), comp_rsrc<TILE_COMPS>(f, 4, V),
+             comp_rsrc<TILE_COMPS>(f, 6, V), comp_rsrc<TILE_COMPS>(f, 8, V), comp_rsrc<TILE_COMPS>(f, 10, V)}};
 }
-static inline bool tile_fits(size_t V, size_t sbytes) { return 2 * V * sbytes < ((size_t)1 << 32); }
+static inline bool rsrc_fits(size_t V, size_t sbytes, int comps) { return comps * V * sbytes < ((size_t)1 << 32); }
+static inline bool tile_fits(size_t V, size_t sbytes) { return rsrc_fits(V, sbytes, TILE_COMPS); }
+static inline bool sap_fits(size_t V) { return rsrc_fits(V, sizeof(float2), SAP_COMPS); }
 // entry `comp` V + `site` of a resource, as complex R
 template <typename S, typename R> __device__ __forceinline__ cx<R> buf_ldc(rsrc_t r, uint32_t site, uint32_t comp) {
     const S v = buf_ld<S>(r, site * (uint32_t)sizeof(S), comp * (uint32_t)sizeof(S));
@@ -227,6 +232,8 @@ __device__ __forceinline__ void tile_clover(const G* ul, int lane, const G* C, u
     if (CL)
         clover_apply<R>([&](int k) { return ldc<G, R>(ul + (72 + ch * 18 + k) * TILE + lane); }, p, res);
     else
-        clover_apply<R>([&](int k) { return buf_ldc<G, R>(comp_rsrc(C, ch * 18 + k / 3 * 3, 3, V), io, k % 3 * V); }, p,
-                        res);
+        clover_apply<R>([&](int k) {
+            return buf_ldc<G, R>(comp_rsrc<TILE_COMPS>(C, ch * 18 + k / TILE_COMPS * TILE_COMPS, V), io,
+                                 k % TILE_COMPS * V);
+        }, p, res);
 }
