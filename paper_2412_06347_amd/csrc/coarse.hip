@@ -29,18 +29,18 @@
 // matrix cores do), so a wave loads its 16 x 16 tiles of operator and vectors
 // along the rows, 64 or 256 bytes a row, and changes lanes in LDS (its own
 // part of it, no barrier).  Slots are exchanged within a row (xor with the row)
-// so that neither side has bank conflicts.  FP64 takes three real products per
-// complex one (with four, the matrix cores, L1 and LDS would each be busy for as
-// long as the other two) and folds the sums of each direction into the result:
-// the error against exact values is 2.6e-15 of the result's norm (2.56e-15 with
-// four products in another order; 2.9e-15 with sums running through all nine
-// directions, three products or four).
-// 48 x 24^3, 24 vectors: FP64, 32 right-hand sides 397 -> 297 us (335 with four
-// products), 12: 226 -> 193, 1: 175 -> 170 (the operator's bytes); FP32, 32: 212
-// -> 193; 32 x 16^3, 20 right-hand sides FP64: 83 -> 52.  Tried for 32 / 20: the
-// row tiles of a site sharing vectors that the workgroup brings in once, a
-// barrier a step, 326 / 67-73; two tiles of right-hand sides a wave, 307 / 67
-// (four products) and 320 / 67 (three): fewer wavefronts cover the loads.
+// so that neither side has bank conflicts.  FP64 folds the sums of each direction
+// into the result: against long double the error is 3.7e-16 of the result's norm
+// (48 columns; 1.35e-15 with one sum through all nine directions).  Three real
+// products per complex one (im = (ar + ai)(br + bi) - ar br - ai bi) take 10 % less
+// time, but the smaller part of a result then carries the rounding of the larger
+// one, and an infinite entry makes it NaN.
+// 48 x 24^3, 24 vectors: FP64, 32 right-hand sides 398 -> 332 us, 12: 223 -> 201,
+// 1: 169 -> 174 (the operator's bytes); FP32, 32: 208 -> 188; 32 x 16^3, 20
+// right-hand sides FP64: 78 -> 65.  Tried for 32 / 20: the row tiles of a site
+// sharing vectors that the workgroup brings in once, a barrier a step, 326 / 67-73;
+// two tiles of right-hand sides a wave, 307 / 67, but half the wavefronts cover the
+// loads of small grids; a sum for each of the four products, the same times.
 template <typename R> struct CoarseTile;
 template <> struct CoarseTile<double> {
     static constexpr int LDS = 2 * 256;      // 16-byte units a wave: operator, vectors
@@ -143,26 +143,20 @@ __global__ __launch_bounds__(512) void k_coarse_mfma(Geo g, int nc, const R* __r
     const int lr = lane & 15, lq = lane >> 4;
     const size_t V1 = g.V1, nn = (size_t)nc * nc;
     const int nk = (nc + 15) / 16, it0 = 9 * nk * dg / DG, it1 = 9 * nk * (dg + 1) / DG;
-    // FP64: three real products per complex one, re = cr - ci, im = c3 - cr - ci
-    V4 cr = {0, 0, 0, 0}, ci = {0, 0, 0, 0}, c3 = {0, 0, 0, 0}, re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+    V4 cr = {0, 0, 0, 0}, ci = {0, 0, 0, 0}, re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
     // FP64: the sums of one direction into those of all
     auto flush = [&]() {
-        re += cr - ci;
-        im += c3 - cr - ci;
-        cr = ci = c3 = V4{0, 0, 0, 0};
+        re += cr;
+        im += ci;
+        cr = ci = V4{0, 0, 0, 0};
     };
     auto mac = [&](const R (&ar)[4], const R (&ai)[4], const R (&br)[4], const R (&bi)[4]) {
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             cr = Mfma<R>::mac(ar[s], br[s], cr);
-            if constexpr (sizeof(R) == 8) {
-                ci = Mfma<R>::mac(ai[s], bi[s], ci);
-                c3 = Mfma<R>::mac(ar[s] + ai[s], br[s] + bi[s], c3);
-            } else {
-                ci = Mfma<R>::mac(ar[s], bi[s], ci);
-                cr = Mfma<R>::mac(-ai[s], bi[s], cr);
-                ci = Mfma<R>::mac(ai[s], br[s], ci);
-            }
+            ci = Mfma<R>::mac(ar[s], bi[s], ci);
+            cr = Mfma<R>::mac(-ai[s], bi[s], cr);
+            ci = Mfma<R>::mac(ai[s], br[s], ci);
         }
     };
     // rows past nc and right-hand sides past nrhs repeat the last one: their results are not written

@@ -144,6 +144,58 @@ def test_coarse_apply_shapes(Nv, n, prec, tol):
     assert relerr(from_dev(y), ref) < tol
 
 
+def coarse_op(pair):
+    import torch
+    nc = 2 * pair.Nv
+    out = torch.empty((pair.bl.V1, 9, nc, nc, 2), dtype=torch.float64, device="cuda")
+    pair.ctx.export_coarse_op(out)
+    return from_dev(out)
+
+
+def test_coarse_apply_small_part():
+    """FP64: the real and the imaginary part of the result each carry the rounding
+    of their own products, also where one is 1e10 times the other.  At a tiny kappa
+    D_1 is the identity to 1e-12, so the imaginary part of the result is that of
+    the vector; the bound is that of a sum of 2 * 9 * 16 products and 9 partial
+    sums in any order, u = 2^-53 a term."""
+    import torch
+    P = Pair((4, 4, 2, 4), (2, 2, 2, 2), 8, kappa=1e-12, oracle_galerkin=False)
+    D = coarse_op(P)
+    x = synth.gaussian_coarse(17, P.bl.V1, 16, 83)
+    x = x.real + 1e-10j * x.imag
+    xd = to_dev(x)
+    y = torch.empty_like(xd)
+    P.ctx.coarse_apply(xd, y)
+    g = x[:, P.nbr]                                              # [n][y][dir][j]
+    s = lambda a, b: np.einsum("ydij,nydj->nyi", a.astype(np.longdouble), b.astype(np.longdouble))   # noqa: E731
+    ref = s(D.real, g.imag) + s(D.imag, g.real)
+    mag = s(np.abs(D.real), np.abs(g.imag)) + s(np.abs(D.imag), np.abs(g.real))
+    err = np.abs(from_dev(y).imag - ref) / mag
+    print("largest error of the small part: %.1f u" % (err.max() * 2 ** 53))
+    assert err.max() <= 300 * 2.0 ** -53
+
+
+def test_coarse_apply_infinite_entry():
+    """An infinite real entry makes both parts of what it multiplies infinite, as
+    re = ar br - ai bi, im = ar bi + ai br do, and nothing else (grid extents of
+    three: every site meets it through one direction only)."""
+    import torch
+    P = Pair((6, 6, 6, 6), (2, 2, 2, 2), 5, oracle_galerkin=False)
+    D = coarse_op(P)
+    n, y0, j = 3, 40, 7
+    x = synth.gaussian_coarse(n, P.bl.V1, 10, 84)
+    xr = torch.from_numpy(np.stack([x.real, x.imag], -1)).cuda()
+    xr[1, y0, j, 0], xr[1, y0, j, 1] = float("inf"), 0.0
+    out = torch.empty_like(xr)
+    P.ctx.coarse_apply(xr, out)
+    got = out.cpu().numpy()
+    want = np.zeros(got.shape)
+    for y, d in zip(*np.nonzero(P.nbr == y0)):
+        want[1, y, :, 0], want[1, y, :, 1] = np.sign(D[y, d, :, j].real), np.sign(D[y, d, :, j].imag)
+    assert not np.isnan(got).any()
+    assert np.array_equal(np.where(np.isinf(got), np.sign(got), 0.0), want)
+
+
 def test_rank_deficient_basis_is_an_error():
     import torch
     from paper_2412_06347_amd import mglma
