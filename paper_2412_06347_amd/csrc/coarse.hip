@@ -17,10 +17,12 @@
 // FP64 / FP32 on the matrix cores (v_mfma_*_16x16x4).
 // grid: the (coarse site, 16-rhs tile) items (site_tile); block: 64 *
 // ceil(nc/16) * DG threads, wave w owns output rows 16w..16w+15 and the 16
-// right-hand sides of the item's tile; with DG > 1 the (direction, 16 columns)
-// steps of a row tile are dealt to DG waves, whose partial sums are added in
-// LDS in a fixed order.  FP64 reads the interleaved complex operator
-// [y][dir][i][j] (the library's D_1 itself), FP32 the planar copy
+// right-hand sides of the item's tile; with DG = 3 three waves take three of a row
+// tile's directions each and their sums are added in LDS.  A wave that has all nine
+// sums the same groups of three and adds them in the same order, so that a
+// right-hand side's bits do not depend on the batch (1-4 % of the time; FP32 error
+// against exact values, 48 columns, 7.2e-7 -> 3.9e-7).  FP64 reads the interleaved
+// complex operator [y][dir][i][j] (the library's D_1 itself), FP32 the planar copy
 // [y][dir][0 = re, 1 = im][i][j].
 //
 // In an MFMA lane (lr, lq) supplies A[row lr][k] and B[k][col lr]: neighbouring
@@ -35,9 +37,9 @@
 // products per complex one (im = (ar + ai)(br + bi) - ar br - ai bi) take 10 % less
 // time, but the smaller part of a result then carries the rounding of the larger
 // one, and an infinite entry makes it NaN.
-// 48 x 24^3, 24 vectors: FP64, 32 right-hand sides 398 -> 332 us, 12: 223 -> 201,
-// 1: 169 -> 174 (the operator's bytes); FP32, 32: 208 -> 188; 32 x 16^3, 20
-// right-hand sides FP64: 78 -> 65.  Tried for 32 / 20: the row tiles of a site
+// 48 x 24^3, 24 vectors: FP64, 32 right-hand sides 398 -> 335 us, 12: 223 -> 204,
+// 1: 169 -> 183 (the operator's bytes); FP32, 32: 208 -> 188; 32 x 16^3, 20
+// right-hand sides FP64: 78 -> 66.  Tried for 32 / 20: the row tiles of a site
 // sharing vectors that the workgroup brings in once, a barrier a step, 326 / 67-73;
 // two tiles of right-hand sides a wave, 307 / 67, but half the wavefronts cover the
 // loads of small grids; a sum for each of the four products, the same times.
@@ -142,13 +144,28 @@ __global__ __launch_bounds__(512) void k_coarse_mfma(Geo g, int nc, const R* __r
     const int m0 = w * 16, n0 = tile * 16;
     const int lr = lane & 15, lq = lane >> 4;
     const size_t V1 = g.V1, nn = (size_t)nc * nc;
-    const int nk = (nc + 15) / 16, it0 = 9 * nk * dg / DG, it1 = 9 * nk * (dg + 1) / DG;
-    V4 cr = {0, 0, 0, 0}, ci = {0, 0, 0, 0}, re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
-    // FP64: the sums of one direction into those of all
+    // groups of three directions, all of them or (DG = 3) one a wave: summed one by one and added in order either way
+    static_assert(DG == 1 || DG == 3, "");
+    const int nk = (nc + 15) / 16, it0 = 3 * nk * dg, it1 = DG == 1 ? 9 * nk : it0 + 3 * nk;
+    V4 cr = {0, 0, 0, 0}, ci = {0, 0, 0, 0}, gr = {0, 0, 0, 0}, gi = {0, 0, 0, 0}, re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+    // FP64: the sums of one direction into those of its group
     auto flush = [&]() {
-        re += cr;
-        im += ci;
+        gr += cr;
+        gi += ci;
         cr = ci = V4{0, 0, 0, 0};
+    };
+    // a group's sums into those of all (DG = 3: left in cr, ci)
+    auto flush_group = [&](bool first) {
+        if constexpr (sizeof(R) == 8) {
+            cr = gr;
+            ci = gi;
+            gr = gi = V4{0, 0, 0, 0};
+        }
+        if constexpr (DG == 1) {
+            re = first ? cr : re + cr;
+            im = first ? ci : im + ci;
+            cr = ci = V4{0, 0, 0, 0};
+        }
     };
     auto mac = [&](const R (&ar)[4], const R (&ai)[4], const R (&br)[4], const R (&bi)[4]) {
 #pragma unroll
@@ -179,15 +196,22 @@ __global__ __launch_bounds__(512) void k_coarse_mfma(Geo g, int nc, const R* __r
             else f.template load<false>(Pr, nn, v, m, nc, k0, lr, lane, zo);
         };
         load(it0);
-        for (int it = it0; it < it1; ++it) {
-            f.put(sh, lr, sizeof(R) == 8 ? lq : lane);
-            if (it + 1 < it1) load(it + 1);
-            wave_lds_fence();
-            R ar[4], ai[4], br[4], bi[4];
-            T::get(sh, lr, lq, ar, ai, br, bi);
-            wave_lds_fence();
-            mac(ar, ai, br, bi);
-            if (sizeof(R) == 8 && (it + 1) % nk == 0) flush();
+        for (int it = it0; it < it1;) {
+            const int g0 = it, g1 = it + 3 * nk;
+            for (int d1 = it + nk; it < g1; ++it) {
+                f.put(sh, lr, sizeof(R) == 8 ? lq : lane);
+                if (it + 1 < it1) load(it + 1);
+                wave_lds_fence();
+                R ar[4], ai[4], br[4], bi[4];
+                T::get(sh, lr, lq, ar, ai, br, bi);
+                wave_lds_fence();
+                mac(ar, ai, br, bi);
+                if (sizeof(R) == 8 && it + 1 == d1) {
+                    flush();
+                    d1 += nk;
+                }
+            }
+            flush_group(g0 == 0);
         }
     } else {
         const size_t mo = (size_t)(m0 + lr < nc ? m0 + lr : nc - 1) * nc;
@@ -208,14 +232,13 @@ __global__ __launch_bounds__(512) void k_coarse_mfma(Geo g, int nc, const R* __r
                 bi[s] = x.y;
             }
             mac(ar, ai, br, bi);
+            if ((it + 1) % (3 * nk) == 0) flush_group(dir == 2);
         }
     }
-    if constexpr (sizeof(R) == 8) {
-        flush();
+    if constexpr (DG == 1) {
         cr = re;
         ci = im;
-    }
-    if constexpr (DG > 1) {
+    } else {
         __syncthreads();
         V4* part = (V4*)shraw;
         if (dg > 0) {
@@ -358,7 +381,8 @@ static int coarse_launch(const Geo& g, int nc, const R* P, const void* in, void*
     typedef typename VT<R>::c2 C2;
     const int ntr = (nc + 15) / 16;
     const dim3 grid(site_tile_grid(g.V1, (nrhs + 15) / 16));
-    // few waves: the steps of a row tile over three of them (16 sites, nc = 16, one right-hand side: 10.3 -> 5.6 us)
+    // few waves: the directions of a row tile over three of them (16 sites, nc = 16, one right-hand side: 10.3 ->
+    // 5.6 us; 512 sites, nc = 32, 48 right-hand sides 66 us, 52 with one).  The sums have the same order either way.
     const int dg = ntr <= 2 && g.V1 * ntr * ((nrhs + 15) / 16) < 2048 ? 3 : 1;
     const size_t shb = (size_t)ntr * dg * CoarseTile<R>::LDS * 16;
     if (dg > 1)

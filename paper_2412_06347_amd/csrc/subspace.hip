@@ -448,9 +448,10 @@ static int restrict_launch(mglma_ctx* c, const BS* B, const void* fine, void* co
     typedef typename VT<R>::c2 C2;
     const Geo& g = c->geo;
     const dim3 grid(g.V1, 2, (nrhs + 15) / 16);
-    // few blocks: eight wavefronts share a block's columns (16 blocks, one right-hand side: 18 -> 12 us; on
-    // 2592 blocks eight cost 430 instead of 380 us)
-    const int nw = (size_t)g.V1 * 2 * grid.z < 512 ? 8 : 4;
+    // few blocks: eight wavefronts share a block's columns (16 blocks, one right-hand side: 18 -> 12 us; 192
+    // blocks, R and T of 12 FP16 78 -> 66; on 2592 blocks eight cost 430 instead of 380 us).  Not by the number of
+    // right-hand sides, as the order of the sums depends on it (192 blocks, 20 FP16 / FP64: 106 -> 96 / 234 -> 245).
+    const int nw = g.V1 < 256 ? 8 : 4;
     const size_t shb = (size_t)nw * 512 * sizeof(R);
     switch ((c->Nv + 15) / 16) {
 #define CASE(N)                                                                                                   \

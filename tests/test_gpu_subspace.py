@@ -144,6 +144,34 @@ def test_coarse_apply_shapes(Nv, n, prec, tol):
     assert relerr(from_dev(y), ref) < tol
 
 
+# the transfers and the coarse operator share out a small grid among more wavefronts: 192 blocks, 1296 blocks
+# with 16 and 10 columns (FP32: in and out of fours), 768 blocks with two row tiles
+@pytest.mark.parametrize("L,Nv", [((8, 8, 8, 6), 12), ((12, 12, 12, 12), 8), ((12, 12, 12, 12), 5), ((12, 8, 8, 16), 12)])
+def test_column_bits_do_not_depend_on_batch(L, Nv):
+    """A right-hand side gives the same bits alone, in a batch of one tile of 16
+    and in one of several."""
+    import torch
+    from paper_2412_06347_amd import mglma
+    ctx = mglma.Context(L, (2, 2, 2, 2), 0.124, 1.0)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda", dtype=torch.float64)   # noqa: E731
+    ctx.load_gauge(0.4 * rnd(ctx.V, 4, 3, 3, 2))      # any 3 x 3 matrices do as links here
+    ctx.build_subspace(rnd(Nv, 12, ctx.V, 2))
+    n, V1, nc = 40, ctx.V // 16, 2 * Nv
+    fine, coarse = rnd(n, 12, ctx.V, 2), rnd(n, V1, nc, 2)
+    calls = [("R", fine, coarse, lambda x, y, p: ctx.restrict(x, y, p)), ("T", coarse, fine, lambda x, y, p: ctx.prolong(x, y, p)),
+             ("D", coarse, coarse, lambda x, y, p: ctx.coarse_apply(x, y, p))]
+    for name, src, dst, call in calls:
+        for prec in (mglma.F64, mglma.F32, mglma.F16 if name != "D" else mglma.BF16):
+            dt = torch.float64 if prec == mglma.F64 else torch.float32
+            x, y = src.to(dt), torch.empty_like(dst, dtype=dt)
+            call(x, y, prec)
+            for k in (1, 16, 17):
+                z = torch.empty_like(y[:k])
+                call(x[:k], z, prec)
+                assert torch.equal(z, y[:k]), (name, prec, k)
+
+
 def coarse_op(pair):
     import torch
     nc = 2 * pair.Nv
