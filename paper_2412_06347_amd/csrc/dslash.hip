@@ -289,6 +289,8 @@ __global__ __launch_bounds__(256, 4) void k_dslash_h(Geo g, const h2* __restrict
 int mg_dslash(mglma_ctx* c, int prec, int gamma5, const void* in, void* out, int nrhs) {
     if (nrhs == 0) return MGLMA_OK;
     const Geo& g = c->geo;
+    // refused: more than 2^31 - 1 tiles of 256 sites, padded as below (2^39 sites of all right-hand sides)
+    if ((size_t)((g.V + 255) / 256 + 7) / 8 * 8 * nrhs > 0x7fffffffu) return MGLMA_ERR_SHAPE;
     if (nrhs >= 2 && tile_fits(g.V, prec_cbytes(prec))) {
         const TileGrid t(g.V, nrhs);
         switch (prec) {
@@ -326,6 +328,7 @@ int mg_dslash(mglma_ctx* c, int prec, int gamma5, const void* in, void* out, int
         return MGLMA_OK;
     }
     const int ntp = ((g.V + 63) / 64 + 7) / 8 * 8;   // tiles, padded to a multiple of the XCD count
+    if ((size_t)ntp * nrhs > 0x7fffffffu) return MGLMA_ERR_SHAPE;
     dim3 grid(ntp * nrhs);
     switch (prec) {
         case MGLMA_F64:

@@ -180,6 +180,17 @@ def test_apply_batch_repeats(prec):
         assert torch.equal(y, first)
 
 
+def test_apply_refuses_too_many_sites():
+    """Sites times right-hand sides past the largest grid: an error, and no launch."""
+    import torch
+    from paper_2412_06347_amd import mglma
+    ctx = mglma.Context((72, 64, 64, 32), (4, 4, 4, 4), 0.124, 1.0)
+    ctx.load_gauge(torch.zeros((ctx.V, 4, 3, 3, 2), dtype=torch.float64, device="cuda"))
+    x, y = torch.zeros(2, device="cuda"), torch.zeros(2, device="cuda")
+    for prec in (mglma.F64, mglma.F32, mglma.F16):
+        assert mglma.lib().mglma_apply_D(ctx._ctx, prec, 0, mglma._ptr(x), mglma._ptr(y), 65535) == -2
+
+
 def test_import_export_roundtrip():
     import torch
     from paper_2412_06347_amd import mglma
