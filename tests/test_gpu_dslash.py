@@ -180,6 +180,34 @@ def test_apply_batch_repeats(prec):
         assert torch.equal(y, first)
 
 
+@pytest.mark.parametrize("L,b,nrhs", [((48, 24, 24, 24), (4, 4, 4, 4), 12), ((8, 4, 6, 5), (2, 4, 3, 5), 5), ((4, 4, 4, 4), (4, 4, 4, 4), 2)],
+                         ids=["full_size", "tail_tile", "one_block"])
+@pytest.mark.parametrize("prec", [0, 1, 2], ids=["f64", "f32", "f16"])
+def test_apply_column_bits(prec, L, b, nrhs):
+    """FP64 and FP32: a right-hand side has the same bits alone and in a batch (the
+    hops, the clover term and their sums in one order), at every site.  FP16 batches
+    also round the projected half spinors, at most 2 max|x|, to FP16: 2^-11 max|x|
+    in each of the 2 * 3 products of eight hops, times kappa max|U|; both results
+    are rounded, 2^-12 max|y| each; 1 % for the FP32 sums."""
+    import torch
+    from paper_2412_06347_amd import mglma
+    ctx = mglma.Context(L, b, 0.124, 1.0)
+    g = torch.Generator(device="cuda").manual_seed(11)
+    U = 0.4 * torch.randn((ctx.V, 4, 3, 3, 2), generator=g, device="cuda", dtype=torch.float64)
+    ctx.load_gauge(U)
+    x, y = ctx.fine(nrhs, prec), ctx.fine(nrhs, prec)
+    x.copy_(torch.randn(x.shape, generator=g, device="cuda", dtype=torch.float32))
+    ctx.apply_D(x, y, prec)
+    z = ctx.fine(1, prec)
+    for q in range(nrhs):
+        ctx.apply_D(x[q:q + 1], z, prec)
+        if prec != mglma.F16:
+            assert torch.equal(z[0], y[q]), q
+        else:
+            most = 0.124 * 48 * float(U.abs().max()) * float(x[q].abs().max()) + float(z.abs().max())
+            assert float((z[0].float() - y[q].float()).abs().max()) <= 1.01 * 2.0 ** -11 * most, q
+
+
 def test_apply_refuses_too_many_sites():
     """Sites times right-hand sides past the largest grid: an error, and no launch."""
     import torch
