@@ -66,11 +66,6 @@ __device__ __forceinline__ uint32_t opaque_v(uint32_t x) {
     asm volatile("" : "+v"(x));
     return x;
 }
-__device__ __forceinline__ int opaque_zero() {
-    int z = 0;
-    asm volatile("" : "+s"(z));
-    return z;
-}
 // Buffer loads and stores: the per-component offset (component x V) is uniform
 // and goes in a scalar register, the site offset is the only vector operand.
 // A resource's bytes stay below 2^32: it spans at most TILE_COMPS components of
