@@ -123,3 +123,38 @@ def test_slots_errors(ens):
     st = pool.take(idz, x)
     assert st[0]["status"] == 0 and float(x.abs().max()) == 0.0
     pool.close()
+
+
+def test_many_right_hand_sides_on_a_small_grid():
+    """192 blocks, where the transfers share a block among more wavefronts, and more
+    right-hand sides than one tile of 16: a batch and a pool of 20 give every
+    solution the bits that it has alone."""
+    import torch
+    from paper_2412_06347_amd import mglma
+    L = (12, 8, 8, 4)
+    ctx = mglma.Context(L, (2, 2, 2, 2), WL["kappa"], WL["csw"])
+    ctx.load_gauge(to_dev(synth.gauge_field(L, WL["eps"], WL["seed"])))
+    tv = ctx.fine(8)
+    ctx.import_fields(to_dev(synth.gaussian_fields(8, L, 1013)), tv)
+    ctx.build_subspace(tv)
+    src = ctx.fine(20)
+    ctx.import_fields(to_dev(synth.gaussian_fields(20, L, 1014)), src)
+    p = mglma.default_params(tol=1e-10, max_outer=30, max_inner=6, gcr_m=6, inner_tol=1e-5, nu_post=2, sap_mr=4,
+                             coarse_iters=4, smoother=mglma.F16, inner=mglma.F32, coarse=mglma.BF16, use_mg=1,
+                             smoother_alg=mglma.SMOOTH_SAP, coarse_eo=1)
+    x = ctx.fine(20)
+    rc, stats = ctx.solve(src, x, p)
+    assert rc == 0
+    pool = mglma.Slots(ctx, 20)
+    ids = pool.load(src)
+    for _ in range(p.max_outer):
+        st = pool.step(p)
+        if all(st[i] != 1 for i in ids):
+            break
+    y = ctx.fine(20)
+    assert all(s["status"] == 0 for s in pool.take(ids, y))
+    pool.close()
+    for k in (0, 7, 15, 16, 19):
+        xa, sa = alone(ctx, src, p, k)
+        assert sa["status"] == 0 and stats[k]["outer"] == sa["outer"]
+        assert torch.equal(x[k], xa[0]) and torch.equal(y[k], xa[0]), k
