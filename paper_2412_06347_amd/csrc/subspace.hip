@@ -370,7 +370,9 @@ __global__ __launch_bounds__(512) void k_restrict(Geo g, int Nv, const BS* __res
 // a copy: sizes as above, against one thread a site on the vector units, FP16
 // basis 461 -> 318 us (4.6 TB/s), FP32 531 -> 520, FP64 1031 -> 860; 3^4
 // blocks, FP64: 38 -> 18 us; 8^4, 4^4 blocks, 8 vectors, one right-hand side:
-// 15 -> 5 us (ns workgroups a block).
+// 15 -> 5 us (ns workgroups a block).  A kernel for every number of steps: with
+// 3, 5, 6, 8 and 16 alone, on 48 x 24^3, FP16 basis, 4 right-hand sides, 16 vectors
+// took 194 instead of 167 us, 36 took 557 instead of 335.
 template <typename R, typename BS, int NS, int W>
 __global__ __launch_bounds__(256) void k_prolong(Geo g, int Nv, const BS* __restrict__ B,
                                                  const typename VT<R>::c2* __restrict__ coarse,
@@ -440,6 +442,66 @@ __global__ __launch_bounds__(256) void k_prolong(Geo g, int Nv, const BS* __rest
     }
 }
 
+// The same sums for few vectors on a large lattice, one thread per fine site:
+// there the matrix cores' time for 16 right-hand sides and a multiple of four
+// vectors exceeds that of the bytes.  The coarse vectors of the workgroup's
+// blocks lie in LDS, PS_RHS right-hand sides at a time; a coarse value serves
+// three basis entries.  48 x 24^3, 4^4 blocks, 5 vectors, 1 / 12 right-hand sides,
+// against the matrix cores: FP16 basis 76 -> 46 / 257 -> 211 us, FP32 102 -> 79 /
+// 265 -> 227, FP64 188 -> 153 / 438 -> 443.
+#define PS_RHS 16
+template <typename R, typename BS>
+__global__ __launch_bounds__(256) void k_prolong_site(Geo g, int Nv, const BS* __restrict__ B,
+                                                      const typename VT<R>::c2* __restrict__ coarse,
+                                                      typename VT<R>::c2* __restrict__ fine, int nrhs, int nbw) {
+    typedef typename VT<R>::c2 C2;
+    extern __shared__ char shraw[];
+    C2* cs = (C2*)shraw;                      // [nbw][nc][PS_RHS]
+    const int i0 = blockIdx.x * 256, i = i0 + threadIdx.x;
+    const int Vb = g.Vb, nc = 2 * Nv, y0 = i0 / Vb, y = i / Vb, l = i - y * Vb;
+    const size_t V = g.V;
+    for (int r0 = 0; r0 < nrhs; r0 += PS_RHS) {
+        const int nr = nrhs - r0 < PS_RHS ? nrhs - r0 : PS_RHS;
+        __syncthreads();
+        for (int e = threadIdx.x; e < nbw * nc * nr; e += 256) {
+            const int r = e % nr, t = e / nr, j = t % nc, yy = y0 + t / nc;
+            cs[t * PS_RHS + r] = yy < g.V1 ? coarse[((size_t)(r0 + r) * g.V1 + yy) * nc + j] : C2{0, 0};
+        }
+        __syncthreads();
+        if (i >= g.V) continue;
+        const C2* cy = cs + (size_t)(y - y0) * nc * PS_RHS;
+        for (int s0 = 0; s0 < 12; s0 += 3) {
+            const int a = s0 / 6;
+            cx<R> acc[3][PS_RHS];
+#pragma unroll
+            for (int u = 0; u < 3; ++u)
+#pragma unroll
+                for (int q = 0; q < PS_RHS; ++q) acc[u][q] = cmk((R)0, (R)0);
+            for (int c = 0; c < Nv; ++c) {
+                const BS* bp = B + (((size_t)y * nc + a * Nv + c) * 6 + s0 - 6 * a) * Vb + l;
+                cx<R> b[3];
+#pragma unroll
+                for (int u = 0; u < 3; ++u) b[u] = ldc<BS, R>(bp + (size_t)u * Vb);
+#pragma unroll
+                for (int q = 0; q < PS_RHS; ++q) {
+                    if (q < nr) {
+                        const cx<R> x = ldc<C2, R>(cy + (a * Nv + c) * PS_RHS + q);
+#pragma unroll
+                        for (int u = 0; u < 3; ++u) cmac(acc[u][q], b[u], x);
+                    }
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < PS_RHS; ++q) {
+                if (q < nr) {
+#pragma unroll
+                    for (int u = 0; u < 3; ++u) stc<C2, R>(fine + ((size_t)(r0 + q) * 12 + s0 + u) * V + i, acc[u][q]);
+                }
+            }
+        }
+    }
+}
+
 // FP32 fields: four columns a lane at once
 static bool cols4(const Geo& g, const void* fine) { return g.Vb % 4 == 0 && (uintptr_t)fine % 16 == 0; }
 
@@ -486,6 +548,17 @@ template <typename R, typename BS, int W>
 static int prolong_launch(mglma_ctx* c, const BS* B, const void* coarse, void* fine, int nrhs) {
     typedef typename VT<R>::c2 C2;
     const Geo& g = c->geo;
+    // Few vectors on a large lattice; by Nv, V and Vb alone, as the order of the sums goes with it.  With up to 131072
+    // sites the matrix cores win (65536, 4^4 blocks, 5 vectors, 5 right-hand sides, FP16 basis: 14 against 21 us), and
+    // with seven vectors on some of the larger ones (294912 sites, FP16: 8 %).
+    const int nbw = 255 / g.Vb + 2;           // blocks that 256 sites can touch
+    const size_t shb = (size_t)nbw * c->nc * PS_RHS * sizeof(C2);
+    if (c->Nv <= 6 && g.V > 131072 && shb <= 64 * 1024) {
+        hipLaunchKernelGGL((k_prolong_site<R, BS>), dim3((g.V + 255) / 256), dim3(256), shb, c->stream, g, c->Nv, B,
+                           (const C2*)coarse, (C2*)fine, nrhs, nbw);
+        HIP_TRY(hipGetLastError());
+        return MGLMA_OK;
+    }
     const int ng = (nrhs + 15) / 16, nt = (6 * g.Vb + 16 * W - 1) / (16 * W);
     // few blocks: ns workgroups share a block's columns, at least four tiles (one a wavefront) each
     long long ns = (1024 + 2LL * g.V1 * ng - 1) / (2LL * g.V1 * ng);
@@ -494,11 +567,25 @@ static int prolong_launch(mglma_ctx* c, const BS* B, const void* coarse, void* f
 #define LAUNCH(NS)                                                                                              \
     hipLaunchKernelGGL((k_prolong<R, BS, NS, W>), grid, dim3(256), 0, c->stream, g, c->Nv, B, (const C2*)coarse, \
                        (C2*)fine, nrhs, (int)ns)
-    if (c->Nv <= 12) LAUNCH(3);
-    else if (c->Nv <= 20) LAUNCH(5);
-    else if (c->Nv <= 24) LAUNCH(6);
-    else if (c->Nv <= 32) LAUNCH(8);
-    else LAUNCH(16);
+    switch ((c->Nv + 3) / 4) {
+        case 1: LAUNCH(1); break;
+        case 2: LAUNCH(2); break;
+        case 3: LAUNCH(3); break;
+        case 4: LAUNCH(4); break;
+        case 5: LAUNCH(5); break;
+        case 6: LAUNCH(6); break;
+        case 7: LAUNCH(7); break;
+        case 8: LAUNCH(8); break;
+        case 9: LAUNCH(9); break;
+        case 10: LAUNCH(10); break;
+        case 11: LAUNCH(11); break;
+        case 12: LAUNCH(12); break;
+        case 13: LAUNCH(13); break;
+        case 14: LAUNCH(14); break;
+        case 15: LAUNCH(15); break;
+        case 16: LAUNCH(16); break;
+        default: return MGLMA_ERR_SHAPE;
+    }
 #undef LAUNCH
     HIP_TRY(hipGetLastError());
     return MGLMA_OK;

@@ -172,6 +172,58 @@ def test_column_bits_do_not_depend_on_batch(L, Nv):
                 assert torch.equal(z, y[:k]), (name, prec, k)
 
 
+# few vectors on lattices past 131072 sites, one thread a site: 4^4, 3^4 and 2^4 blocks, a part of a workgroup at the
+# end, one tile of 16 right-hand sides and more; the first sizes past that on the matrix cores (131072 sites, seven vectors)
+@pytest.mark.parametrize("L,b,Nv,n", [((24, 24, 16, 16), (4, 4, 4, 4), 1, 17), ((30, 18, 18, 15), (3, 3, 3, 3), 5, 3),
+                                      ((26, 18, 18, 16), (2, 2, 2, 2), 6, 33), ((32, 16, 16, 16), (4, 4, 4, 4), 6, 2),
+                                      ((30, 18, 18, 15), (3, 3, 3, 3), 7, 2)])
+def test_prolong_few_vectors(L, b, Nv, n):
+    """T c of few vectors against sums over the exported basis in FP64, and the
+    same bits for a column in the batch and alone.  A part of the result is a sum of 2 Nv products with a rounding
+    each of at most half a spacing of the sum of their sizes, the reference has three for two products: (5 Nv) / 2
+    spacings for a part, 4 Nv for both."""
+    import torch
+    from paper_2412_06347_amd import mglma
+    ctx = mglma.Context(L, b, 0.124, 1.0)
+    g = torch.Generator(device="cuda").manual_seed(17)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda", dtype=torch.float64)   # noqa: E731
+    ctx.load_gauge(0.4 * rnd(ctx.V, 4, 3, 3, 2))
+    ctx.build_subspace(rnd(Nv, 12, ctx.V, 2))
+    Vb = int(np.prod(b))
+    V1, nc = ctx.V // Vb, 2 * Nv
+    B = torch.empty((V1, nc, Vb, 4, 3, 2), dtype=torch.float64, device="cuda")
+    ctx.export_basis(B)
+    c = rnd(n, V1, nc, 2)
+    B = torch.view_as_complex(B)
+    unit = torch.zeros((nc, V1, nc, 2), dtype=torch.float32, device="cuda")
+    unit[range(nc), :, range(nc), 0] = 1.0
+    for prec, dt in ((mglma.F64, torch.float64), (mglma.F32, torch.float32), (mglma.F16, torch.float32)):
+        x = c.to(dt)
+        y = torch.empty((n, 12, ctx.V, 2), dtype=dt, device="cuda")
+        ctx.prolong(x, y, prec)
+        Bc = torch.view_as_complex(torch.view_as_real(B).to(dt).double())
+        if prec == mglma.F16:   # the FP16 basis itself: rounded by half a spacing, from FP64 or (another 2^-24) FP32
+            e = torch.empty((nc, 12, ctx.V, 2), dtype=dt, device="cuda")
+            ctx.prolong(unit, e, prec)
+            Bc = torch.view_as_complex(e.double()).reshape(nc, 4, 3, V1, Vb).permute(3, 0, 4, 1, 2)
+            d, m = torch.view_as_real(Bc - B).abs(), torch.view_as_real(B).abs()
+            assert bool((d <= (2.0 ** -11 + 2.0 ** -23) * m + 2.0 ** -25).all())
+        eps = 4 * Nv * torch.finfo(dt).eps
+        for k in range(0, n, 2):
+            ref, size = 0, 0
+            xk = torch.view_as_complex(x[k].double())
+            for j in range(nc):
+                ref = ref + Bc[:, j] * xk[:, j, None, None, None]
+                size = size + Bc[:, j].abs() * xk[:, j, None, None, None].abs()
+            got = torch.view_as_complex(y[k].double()).reshape(4, 3, V1, Vb).permute(2, 3, 0, 1)
+            far = int(((got - ref).abs() > eps * size).sum())
+            assert far == 0, (prec, k, far)
+            z = torch.empty_like(y[:1])
+            ctx.prolong(x[k:k + 1], z, prec)
+            assert torch.equal(z[0], y[k]), (prec, k)
+    ctx.close()
+
+
 def coarse_op(pair):
     import torch
     nc = 2 * pair.Nv
