@@ -109,6 +109,37 @@ def test_transfer_shapes(b, Nv, n, shift, prec, tol):
     assert float(buf[:2 * shift].abs().sum()) == 0 and float(buf[2 * shift + src.numel():].abs().sum()) == 0
 
 
+# 256 and 511 blocks of 48 sites, 1022 of 24, 256 of 42 and 512 of 48: eight or four wavefronts a block
+@pytest.mark.parametrize("L,b", [((8, 16, 8, 12), (2, 4, 2, 3)), ((14, 292, 2, 3), (2, 4, 2, 3)),
+                                 ((14, 292, 2, 3), (2, 4, 1, 3)), ((8, 28, 12, 4), (2, 7, 3, 1)),
+                                 ((16, 16, 8, 12), (2, 4, 2, 3))])
+@pytest.mark.parametrize("prec,tol", [(0, 1e-12), (1, 2e-6), (2, 1e-3)])
+def test_restrict_many_blocks(L, b, prec, tol):
+    """R x against sums over the exported basis, and the same bits for a column alone."""
+    import torch
+    from paper_2412_06347_amd import mglma
+    ctx = mglma.Context(L, b, 0.124, 1.0)
+    g = torch.Generator(device="cuda").manual_seed(23)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda", dtype=torch.float64)   # noqa: E731
+    Nv, n, Vb = 5, 17, int(np.prod(b))
+    V1, dt = ctx.V // Vb, torch.float64 if prec == 0 else torch.float32
+    ctx.load_gauge(0.4 * rnd(ctx.V, 4, 3, 3, 2))
+    ctx.build_subspace(rnd(Nv, 12, ctx.V, 2))
+    B = torch.empty((V1, 2 * Nv, Vb, 4, 3, 2), dtype=torch.float64, device="cuda")
+    ctx.export_basis(B)
+    B = torch.view_as_complex(B)
+    x = rnd(n, 12, ctx.V, 2).to(dt)
+    y, z = torch.empty((n, V1, 2 * Nv, 2), dtype=dt, device="cuda"), torch.empty((1, V1, 2 * Nv, 2), dtype=dt, device="cuda")
+    ctx.restrict(x, y, prec)
+    for k in range(n):
+        f = torch.view_as_complex(x[k].double()).reshape(4, 3, V1, Vb).permute(2, 3, 0, 1)
+        ref = (B.conj() * f[:, None]).sum((2, 3, 4))
+        assert relerr(from_dev(y[k]), ref.cpu().numpy()) < tol
+        ctx.restrict(x[k:k + 1], z, prec)
+        assert torch.equal(z[0], y[k])
+    ctx.close()
+
+
 @pytest.mark.parametrize("prec,tol", [(0, 1e-12), (1, 2e-6), (3, 2e-2)])
 @pytest.mark.parametrize("gamma5", [0, 1])
 def test_coarse_apply_parity(pair, prec, tol, gamma5):
