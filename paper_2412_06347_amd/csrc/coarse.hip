@@ -129,7 +129,7 @@ template <> struct CoarseTile<float> {
 // VEC = false (FP32 with nc not a multiple of four): entries loaded one by one,
 // straight into the lanes that multiply them
 template <typename R, bool VEC, int DG>
-__global__ __launch_bounds__(512) void k_coarse_mfma(Geo g, int nc, const R* __restrict__ P,
+__global__ __launch_bounds__(DG == 1 ? 512 : 768) void k_coarse_mfma(Geo g, int nc, const R* __restrict__ P,
                                                      const typename VT<R>::c2* __restrict__ in,
                                                      typename VT<R>::c2* __restrict__ out, int nrhs, int gamma5) {
     typedef typename VT<R>::c2 C2;
@@ -382,8 +382,11 @@ static int coarse_launch(const Geo& g, int nc, const R* P, const void* in, void*
     const int ntr = (nc + 15) / 16;
     const dim3 grid(site_tile_grid(g.V1, (nrhs + 15) / 16));
     // few waves: the directions of a row tile over three of them (16 sites, nc = 16, one right-hand side: 10.3 ->
-    // 5.6 us; 512 sites, nc = 32, 48 right-hand sides 66 us, 52 with one).  The sums have the same order either way.
-    const int dg = ntr <= 2 && g.V1 * ntr * ((nrhs + 15) / 16) < 2048 ? 3 : 1;
+    // 5.6 us; 512 sites, nc = 32, 48 right-hand sides 66 us, 52 with one).  With three or four row tiles, nine or
+    // twelve waves, up to one workgroup a compute unit (4 sites, FP64, nc = 48: 29 -> 23 us, nc = 64: 38 -> 31; 324 sites,
+    // nc = 64: 2-7 % slower).  The sums have the same order either way.
+    const long items = (long)g.V1 * ((nrhs + 15) / 16);
+    const int dg = ntr <= 2 ? (items * ntr < 2048 ? 3 : 1) : ntr <= 4 && items <= 256 ? 3 : 1;
     const size_t shb = (size_t)ntr * dg * CoarseTile<R>::LDS * 16;
     if (dg > 1)
         hipLaunchKernelGGL((k_coarse_mfma<R, VEC, 3>), grid, dim3(64 * ntr * dg), shb, stream, g, nc, P, (const C2*)in,

@@ -176,8 +176,9 @@ def test_coarse_apply_shapes(Nv, n, prec, tol):
 
 
 # the transfers and the coarse operator share out a small grid among more wavefronts: 192 blocks, 1296 blocks
-# with 16 and 10 columns (FP32: in and out of fours), 768 blocks with two row tiles
-@pytest.mark.parametrize("L,Nv", [((8, 8, 8, 6), 12), ((12, 12, 12, 12), 8), ((12, 12, 12, 12), 5), ((12, 8, 8, 16), 12)])
+# with 16 and 10 columns (FP32: in and out of fours), 768 blocks with two row tiles, 192 with three and four
+@pytest.mark.parametrize("L,Nv", [((8, 8, 8, 6), 12), ((12, 12, 12, 12), 8), ((12, 12, 12, 12), 5), ((12, 8, 8, 16), 12),
+                                  ((8, 8, 8, 6), 21), ((8, 8, 8, 6), 32)])
 def test_column_bits_do_not_depend_on_batch(L, Nv):
     """A right-hand side gives the same bits alone, in a batch of one tile of 16
     and in one of several."""
