@@ -303,8 +303,10 @@ int mg_dslash(mglma_ctx* c, int prec, int gamma5, const void* in, void* out, int
             case MGLMA_F32:
                 // the clover term in LDS as well from four right-hand sides on: 55 instead of 37 KB a
                 // workgroup, so two instead of four on a compute unit, which costs batches of two or three
-                // (48 x 24^3: 2 rhs 204 against 264 us, 3: 271 / 281, 4: 342 / 323, 12: 948 / 828)
-                if (nrhs < 4)
+                // (48 x 24^3: 2 rhs 204 against 264 us, 3: 271 / 281, 4: 342 / 323, 12: 948 / 828), and not where two on
+                // a compute unit leave up to half as many for a second round (24 x 12^3, 648 workgroups: 5 rhs 24 against
+                // 33 us, 9: 38 / 47, 16: 63 / 62; 32 x 12^3, 864: 5 rhs 31 / 34, 9: 49 / 49, 16: 84 / 71)
+                if (nrhs < 4 || (t.nt * t.ng > 512 && t.nt * t.ng <= 768))
                     hipLaunchKernelGGL((k_dslash_tile<float2, float2, float, false, 4>), t.grid, t.block, 0, c->stream,
                                        g, (const float2*)in, (float2*)out, c->U32, c->C32, (float)c->kappa, gamma5,
                                        nrhs, t.nt, t.ng);

@@ -180,8 +180,8 @@ def test_apply_batch_repeats(prec):
         assert torch.equal(y, first)
 
 
-@pytest.mark.parametrize("L,b,nrhs", [((48, 24, 24, 24), (4, 4, 4, 4), 12), ((8, 4, 6, 5), (2, 4, 3, 5), 5), ((4, 4, 4, 4), (4, 4, 4, 4), 2)],
-                         ids=["full_size", "tail_tile", "one_block"])
+@pytest.mark.parametrize("L,b,nrhs", [((48, 24, 24, 24), (4, 4, 4, 4), 12), ((8, 4, 6, 5), (2, 4, 3, 5), 5), ((4, 4, 4, 4), (4, 4, 4, 4), 2),
+                                      ((24, 12, 12, 12), (4, 4, 4, 4), 5)], ids=["full_size", "tail_tile", "one_block", "second_round"])
 @pytest.mark.parametrize("prec", [0, 1, 2], ids=["f64", "f32", "f16"])
 def test_apply_column_bits(prec, L, b, nrhs):
     """FP64 and FP32: a right-hand side has the same bits alone and in a batch (the
