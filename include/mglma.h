@@ -438,7 +438,9 @@ int mglma_solve(mglma_ctx* ctx, const mglma_solve_params* p, const double* b_dev
  *     A slot finishes when |r| <= p->tol |b| (state 2), with
  *     MGLMA_ERR_NOT_CONVERGED after p->max_outer cycles or
  *     MGLMA_ERR_NONFINITE; a slot's arithmetic is that of mglma_solve on it
- *     alone whatever else runs.  status (host, may be NULL) receives the
+ *     alone whatever else runs (with FP16 MR or CA-GCR smoothing up to the
+ *     rounding of its FP16 applies, which one right-hand side alone computes
+ *     in FP32).  status (host, may be NULL) receives the
  *     state of every slot id: 0 free, 1 running, 2 converged, < 0 failed.
  *     Synchronising.  Errors: ARG, NO_SUBSPACE (use_mg), HIP.
  *   mglma_slots_take: copy the solutions of n finished slots to x_dev

@@ -597,7 +597,8 @@ static int prolong_launch(mglma_ctx* c, const BS* B, const void* coarse, void* f
 int mg_prolong(mglma_ctx* c, int prec, const void* coarse, void* fine, int nrhs) {
     if (nrhs <= 0) return MGLMA_OK;
     const Geo& g = c->geo;
-    // blocks of few sites with many vectors are refused
+    // Blocks of few sites with many vectors are refused: the coarse vectors of the blocks that 256 sites touch, past 48
+    // KB.  No kernel here needs that; the shapes that T takes do not change with its kernels.
     const size_t cb = prec == MGLMA_F64 ? sizeof(cx<double>) : sizeof(cx<float>);
     if ((size_t)(255 / g.Vb + 2) * c->nc * cb > 48 * 1024) return MGLMA_ERR_SHAPE;
     const bool v = cols4(g, fine);
