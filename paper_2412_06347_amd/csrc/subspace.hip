@@ -511,12 +511,12 @@ static int restrict_launch(mglma_ctx* c, const BS* B, const void* fine, void* co
     const Geo& g = c->geo;
     const dim3 grid(g.V1, 2, (nrhs + 15) / 16);
     // few blocks: eight wavefronts share a block's columns (16 blocks, one right-hand side: 18 -> 12 us; 192
-    // blocks, R and T of 12 FP16 78 -> 66), with at least two chunks of columns for each up to 511 blocks (288 blocks
-    // of 4^4, 16 vectors, 1 / 12 / 20 right-hand sides: FP16 34 -> 29 / 37 -> 30 / 50 -> 48 us, FP32 36 -> 31 / 39 -> 34
-    // / 57 -> 57, FP64 57 -> 52 / 90 -> 89 / 129 -> 138).  From 512 blocks on four: 20 there 73 against 80.  Not by the
-    // number of right-hand sides, as the order of the sums depends on it (192 blocks, 20 FP16 / FP64: 106 -> 96 / 234 ->
-    // 245).
-    const int nw = g.V1 < (6 * g.Vb >= 256 ? 512 : 256) ? 8 : 4;
+    // blocks, R and T of 12 FP16 78 -> 66), in FP32 with at least two chunks of columns for each up to 511 blocks (288
+    // blocks of 4^4, 16 vectors, 1 / 12 / 20 right-hand sides: FP16 basis 34 -> 29 / 37 -> 30 / 50 -> 48 us, FP32 36 ->
+    // 31 / 39 -> 34 / 57 -> 57; FP64 on 384 blocks of 3^4, 10 vectors, 5: R and T 42 with four, 47 with eight).  From 512
+    // blocks on four: 20 there 73 against 80.  Not by the number of right-hand sides, as the order of the sums depends on
+    // it (192 blocks, 20 FP16 / FP64: 106 -> 96 / 234 -> 245).
+    const int nw = g.V1 < (sizeof(R) == 4 && 6 * g.Vb >= 256 ? 512 : 256) ? 8 : 4;
     const size_t shb = (size_t)nw * 512 * sizeof(R);
     switch ((c->Nv + 15) / 16) {
 #define CASE(N)                                                                                                   \
